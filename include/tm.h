@@ -213,8 +213,8 @@ typedef struct tm_batch tm_batch;
 /* Plan the retrieval of n problems with the same options (method ER or
  * ER_CYCLIC; start GIVEN, BACKPROP, SPECTRAL or LANCZOS). Every iteration is one persistent
  * launch whose work items are (problem, row tile): 1 row of 8192 modes, 2 of
- * 4096, 4 of 2048 or 8 of 1024, each run with its grid's FFT specialisation
- * and the digit order chosen by tm_set_variant. With use_graph = 1 the whole
+ * 4096, 4 of 2048 or 8 of 1024, each run with its grid's FFT specialisation.
+ * With use_graph = 1 the whole
  * sequence (start, iterations, FP64 residuals, stats) is captured once into a
  * HIP graph. The plan keeps the problem pointers: tm_batch_run reuses them.
  * Allocates its workspace here (not in tm_batch_run). */
@@ -244,10 +244,13 @@ int tm_set_variant(tm_ctx *ctx, int32_t n1, int32_t n2, int32_t variant);
  * gradient kernels of the L-BFGS solvers (Alg. 1 and its amplitude-cost form)
  * and the amplitude cost's line search; every other kernel keeps the default
  * plan of the same digit order. The batch
- * (tm_batch_create) takes bit 0 only, so its rows equal single-problem runs in
- * configurations 0 and 1.
+ * (tm_batch_create) runs the kernels of configurations 0 and 1, so its rows
+ * equal single-problem runs in those.
  * They are compiled for the 32x32, 64x32, 64x64 and 128x64 grids (twice the
  * rows only where a workgroup stays at 512 threads or fewer).
+ * On those grids configurations 0 and 1 run kernels whose FFT passes mix both
+ * axes (one row of N/16 threads per workgroup, of both digit orders the same);
+ * their tm_config_info entry is the shape of the one-axis kernels.
  *
  * tm_config_info: 1 if configuration cfg is compiled for the grid, with its
  * threads per workgroup, rows per workgroup and values per thread (each

@@ -9,7 +9,7 @@ namespace tmk {
 
 constexpr int BATCH_WG = 512;
 
-// Grids the batched kernel is compiled for; code = 2 * grid_id + variant.
+// Grids the batched kernel is compiled for (BatchProb::code).
 // 0: 32 x 32, 1: 64 x 32, 2: 64 x 64, 3: 128 x 64.
 int batch_grid_id(int n1, int n2);
 // rows per work item (rows of that grid one 512-thread workgroup handles)

@@ -2,7 +2,7 @@
 // tile of one problem (1 row of 8192 modes, 2 of 4096, 4 of 2048, 8 of
 // 1024: tiles of similar FFT work); workgroups stride over the item list, and
 // each item runs the same fused row body as the single-problem kernels,
-// specialised for its grid and FFT digit order.
+// specialised for its grid. Two 512-thread workgroups share a CU (LDS and registers).
 #include <hip/hip_runtime.h>
 
 #include "batch.hpp"
@@ -20,10 +20,10 @@ int batch_grid_id(int n1, int n2) {
 
 int batch_rows_per_item(int g) {
   switch (g) {
-    case 0: return Launch<Plan<5, 5>, BATCH_WG>::RPW;
-    case 1: return Launch<Plan<6, 5>, BATCH_WG>::RPW;
-    case 2: return Launch<Plan<6, 6>, BATCH_WG>::RPW;
-    case 3: return Launch<Plan<7, 6>, BATCH_WG>::RPW;
+    case 0: return Launch<WidePlan<5, 5>, BATCH_WG>::RPW;
+    case 1: return Launch<WidePlan<6, 5>, BATCH_WG>::RPW;
+    case 2: return Launch<WidePlan<6, 6>, BATCH_WG>::RPW;
+    case 3: return Launch<WidePlan<7, 6>, BATCH_WG>::RPW;
   }
   return 0;
 }
@@ -35,7 +35,8 @@ constexpr int lds_of() {
   return Launch<PL, BATCH_WG>::LDS_ELEMS;
 }
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
-constexpr int kLds = cmax(cmax(lds_of<Plan<5, 5>>(), lds_of<Plan<6, 5>>()), cmax(lds_of<Plan<6, 6>>(), lds_of<Plan<7, 6>>()));
+constexpr int kLds = cmax(cmax(lds_of<WidePlan<5, 5>>(), lds_of<WidePlan<6, 5>>()), cmax(lds_of<WidePlan<6, 6>>(), lds_of<WidePlan<7, 6>>()));
+static_assert(kLds * 8 + 1024 <= 80 * 1024, "two workgroups per CU");
 
 // Launch-wide values the item bodies need. They reach the out-of-line bodies as
 // scalars: a struct passed to a non-inlined function goes through private
@@ -141,9 +142,9 @@ __device__ __attribute__((noinline)) void item_body(const BatchProb* probs, cons
 }
 
 template <int MODE, typename IT, bool SUMS>
-__global__ void __launch_bounds__(BATCH_WG) batch_kernel(BatchArgs b) {
+__global__ void __launch_bounds__(BATCH_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) batch_kernel(BatchArgs b) {
   __shared__ cx<float> lds[kLds];
-  __shared__ float red[Launch<Plan<7, 6>, BATCH_WG>::RED_FLOATS];
+  __shared__ float red[Launch<WidePlan<7, 6>, BATCH_WG>::RED_FLOATS];
   constexpr int M = (MODE == BATCH_ER) ? M_ER : (MODE == BATCH_ERC) ? M_ERC : (MODE == BATCH_LZ) ? M_LANCZOS : M_SPEC;
   for (int it = blockIdx.x; it < b.n_items; it += gridDim.x) {
     const int code = b.probs[b.items[it].prob].code;
@@ -151,14 +152,10 @@ __global__ void __launch_bounds__(BATCH_WG) batch_kernel(BatchArgs b) {
   item_body<__VA_ARGS__, M, MODE, IT, SUMS>(b.probs, b.items, it, b.tw32, b.tau, b.momentum, b.lower, b.er_beta, \
                                             b.swap, b.lz_j, b.lz_fuse, b.lz_k, lds, red)
     switch (code) {
-      case 0: TM_ITEM(Plan<5, 5, -1, 0>); break;
-      case 1: TM_ITEM(Plan<5, 5, -1, 1>); break;
-      case 2: TM_ITEM(Plan<6, 5, -1, 0>); break;
-      case 3: TM_ITEM(Plan<6, 5, -1, 1>); break;
-      case 4:
-      case 5: TM_ITEM(Plan<6, 6, -1, 0>); break;
-      case 6: TM_ITEM(Plan<7, 6, -1, 0>); break;
-      case 7: TM_ITEM(Plan<7, 6, -1, 1>); break;
+      case 0: TM_ITEM(WidePlan<5, 5>); break;
+      case 1: TM_ITEM(WidePlan<6, 5>); break;
+      case 2: TM_ITEM(WidePlan<6, 6>); break;
+      case 3: TM_ITEM(WidePlan<7, 6>); break;
       default: break;
     }
 #undef TM_ITEM

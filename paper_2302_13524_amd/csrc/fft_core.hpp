@@ -23,8 +23,10 @@
 namespace tmk {
 
 // ------------------------------------------------------------------ complex
+// 8-byte aligned, so that an FP32 value moves between registers and LDS or
+// global memory as one 64-bit access.
 template <typename T>
-struct cx {
+struct alignas(8) cx {
   T x, y;
 };
 template <typename T>
@@ -47,6 +49,11 @@ template <typename T>
 __device__ __forceinline__ cx<T> cmulc(cx<T> a, cx<T> b) {
   return {fmadd(a.x, b.x, a.y * b.y), fmadd(a.y, b.x, -(a.x * b.y))};
 }
+// Re conj(a) b, and c + s a
+template <typename T>
+__device__ __forceinline__ T rdot(cx<T> a, cx<T> b) { return fmadd(a.x, b.x, a.y * b.y); }
+template <typename T>
+__device__ __forceinline__ cx<T> axpy(T s, cx<T> a, cx<T> c) { return {fmadd(s, a.x, c.x), fmadd(s, a.y, c.y)}; }
 template <typename T>
 __device__ __forceinline__ cx<T> scl(cx<T> a, T s) { return {a.x * s, a.y * s}; }
 // multiply by -j (forward) or +j (inverse)
@@ -215,6 +222,8 @@ constexpr int default_le(int ln) { return ln >= 4 ? 4 : ln; }
 // VAR_ selects the digit order (see digit_bits); the autotuner picks it per grid.
 template <int L1_, int L2_, int LE_ = -1, int VAR_ = 0>
 struct Plan {
+  static constexpr bool WIDE = false;
+  static constexpr int WAVES = 2;  // per SIMD
   static constexpr int VAR = VAR_;
   static constexpr int L1 = L1_, L2 = L2_;
   static constexpr int LN = L1 + L2;
@@ -229,6 +238,7 @@ struct Plan {
   // LDS: row-major grid with one pad slot after every n2 slots (n2 >= 16)
   static constexpr int PADSH = (L2 >= 4) ? L2 : 30;
   static constexpr int LDS_ROW = N + ((L2 >= 4) ? N1 : 0);
+  static constexpr int LDS_TW = 0;
   static __device__ __forceinline__ int lds_addr(int e) { return e + (e >> PADSH); }
 };
 
@@ -438,28 +448,18 @@ __device__ __forceinline__ const cx<T>* tw_of(const Tw<T>& tw) {
   return (PassGeo<PL, P>::AXIS == 1) ? tw.t1 : tw.t2;
 }
 
-// LDS exchange buffers of one row. With two buffers (alt != 0) exchange k
-// writes buffer k % 2, so one barrier per exchange suffices: every thread's
-// reads of exchange k-1 precede its writes of exchange k, and the barrier of
-// exchange k orders all of them before the reads of exchange k; the writes of
-// exchange k+1 go to the other buffer. With one buffer a second barrier
-// protects the reads of the previous exchange.
-template <typename T>
-struct Xbuf {
-  cx<T>* base;
-  int alt;     // element offset of the second buffer, 0 if single-buffered
-  int parity;  // buffer of the next exchange
-  __device__ __forceinline__ cx<T>* next() {
-    cx<T>* p = base + (parity ? alt : 0);
-    parity ^= (alt != 0);
-    return p;
-  }
-};
-
+// One LDS copy of the row serves every exchange, with one barrier each: a pass
+// writes its values at the slots which the same thread read them from, so no
+// other thread's pending read is overwritten. That holds while each transform
+// starts in the layout the last one ended in (forward and inverse alternate);
+// otherwise a barrier goes between them (LineFft::fence).
 template <class PL, int PW, int PR, typename T>
-__device__ __forceinline__ void exchange(cx<T>* x, Xbuf<T>& xb, int ltid) {
-  cx<T>* lds = xb.next();
-  if (xb.alt == 0) __syncthreads();
+__device__ __forceinline__ void exchange(cx<T>* x, cx<T>* lds, int ltid) {
+  // FP64, 1024 threads: a barrier that keeps the workgroup's 16 waves in step, though no
+  // value needs it (residual at 2286 x 8192: 345 us with it, 410 without; smaller grids
+  // are faster without, 512 x 1024: 15.5 us against 22.8)
+  if constexpr (sizeof(T) == 8 && PL::T >= 1024) __syncthreads();
+  else if constexpr (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);  // registers: nothing moves across the exchange
   lds_store<PL, PW, T>(lds, x, ltid);
   __syncthreads();
   lds_load<PL, PR, T>(lds, x, ltid);
@@ -468,11 +468,11 @@ __device__ __forceinline__ void exchange(cx<T>* x, Xbuf<T>& xb, int ltid) {
 // Full forward DFT: x enters in the layout of pass 0 (natural element values),
 // leaves in the layout of the last pass holding the digit-reversed spectrum.
 template <class PL, int P, typename T>
-__device__ __forceinline__ void fwd_from(cx<T>* x, Xbuf<T>& xb, int ltid, const Tw<T>& tw) {
+__device__ __forceinline__ void fwd_from(cx<T>* x, cx<T>* lds, int ltid, const Tw<T>& tw) {
   if constexpr (P < PL::NP) {
-    if constexpr (P > 0) exchange<PL, P - 1, P, T>(x, xb, ltid);
+    if constexpr (P > 0) exchange<PL, P - 1, P, T>(x, lds, ltid);
     fwd_pass<PL, P, T>(x, ltid, tw_of<PL, P, T>(tw));
-    fwd_from<PL, P + 1, T>(x, xb, ltid, tw);
+    fwd_from<PL, P + 1, T>(x, lds, ltid, tw);
   }
 }
 
@@ -483,24 +483,32 @@ struct NoHook {
 };
 
 template <class PL, int P, typename T, class H>
-__device__ __forceinline__ void inv_from(cx<T>* x, Xbuf<T>& xb, int ltid, const Tw<T>& tw, const H& before_last) {
+__device__ __forceinline__ void inv_from(cx<T>* x, cx<T>* lds, int ltid, const Tw<T>& tw, const H& before_last) {
   if constexpr (P >= 0) {
-    if constexpr (P < PL::NP - 1) exchange<PL, P + 1, P, T>(x, xb, ltid);
+    if constexpr (P < PL::NP - 1) exchange<PL, P + 1, P, T>(x, lds, ltid);
     if constexpr (P == 0) before_last();
     inv_pass<PL, P, T>(x, ltid, tw_of<PL, P, T>(tw));
-    inv_from<PL, P - 1, T>(x, xb, ltid, tw, before_last);
+    inv_from<PL, P - 1, T>(x, lds, ltid, tw, before_last);
   }
 }
 
+// Transforms of one row group: forward() takes x in the layout of the first pass
+// and leaves it in that of the last one, inverse() the other way round.
 template <class PL, typename T>
-__device__ __forceinline__ void fft_forward(cx<T>* x, Xbuf<T>& xb, int ltid, const Tw<T>& tw) {
-  fwd_from<PL, 0, T>(x, xb, ltid, tw);
-}
-template <class PL, typename T, class H = NoHook>
-__device__ __forceinline__ void fft_inverse(cx<T>* x, Xbuf<T>& xb, int ltid, const Tw<T>& tw,
-                                            const H& before_last = H{}) {
-  inv_from<PL, PL::NP - 1, T>(x, xb, ltid, tw, before_last);
-}
+struct LineFft {
+  cx<T>* lds;
+  int ltid;
+  Tw<T> tw;
+  __device__ __forceinline__ LineFft(cx<T>* l, cx<T>*, int lt, const cx<T>* t1, const cx<T>* t2) : lds(l), ltid(lt), tw(t1, t2) {}
+  __device__ __forceinline__ void forward(cx<T>* x) const { fwd_from<PL, 0, T>(x, lds, ltid, tw); }
+  template <class H = NoHook>
+  __device__ __forceinline__ void inverse(cx<T>* x, const H& before_last = H{}) const {
+    inv_from<PL, PL::NP - 1, T>(x, lds, ltid, tw, before_last);
+  }
+  __device__ __forceinline__ void fence() const {
+    if constexpr (PL::NP > 1) __syncthreads();
+  }
+};
 
 // Digit reversal of one axis: slot index s (digits high to low as laid out by
 // the DIF passes) -> frequency index k = d_0 + R_0 d_1 + R_0 R_1 d_2 + ...

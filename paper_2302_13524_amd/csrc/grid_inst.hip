@@ -3,6 +3,8 @@
 #include "row_kernels.hpp"
 #include "grids.hpp"
 
+#include <type_traits>
+
 #ifndef GL1
 #error "GL1 / GL2 must be defined"
 #endif
@@ -15,6 +17,18 @@ namespace tmk {
 // FP64 residual: 8 values per thread (at 128 x 64: 1024 threads, 128 VGPRs, four
 // waves per SIMD; 16 values per thread took 248 VGPRs and two waves)
 using PLd = Plan<GL1, GL2, (GL1 + GL2 >= 3) ? 3 : GL1 + GL2>;
+
+// Configurations 0 and 1: the mixed-axis plan where it is compiled (32 x 32 to
+// 128 x 64; it has no digit order), else one axis per pass in either digit
+// order. At 2286 x 8192 it runs the Lanczos step in 287 us against 384, the
+// cyclic sweep in 251 against 372 and the gradient in 250 against 379; at
+// 1500 x 4096 85 against 103, 73 against 99 and 78 against 105; at 512 x 1024
+// 23 against 27, 22 against 27 and 25 against 27. With few rows it is the faster
+// one as well or level (64 x 8192: cyclic sweep 36 us against 40, Lanczos step
+// 40 and 40; 100 x 1024: 21 against 27, 22 against 27), so no row count decides.
+constexpr bool kWide = wide_compiled(GL1, GL2);
+template <int VAR>
+using Default = std::conditional_t<kWide, WidePlan<kWide ? GL1 : 6, kWide ? GL2 : 6>, Plan<GL1, GL2, -1, VAR>>;
 
 template <class PLg, typename IT>
 static int launch_t(int mode, const RowArgs& a, hipStream_t s) {
@@ -71,18 +85,17 @@ constexpr bool kHasVar = uneven(GL1) || uneven(GL2);
 
 int TM_CAT(row_launch, GL1, GL2)(int mode, int ibf16, const RowArgs& a, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  using P0 = Plan<GL1, GL2>;
+  using P0 = Default<0>;
   return ibf16 ? launch_t<P0, uint16_t>(mode, a, s) : launch_t<P0, float>(mode, a, s);
 }
 
 int TM_CAT(row_launchv, GL1, GL2)(int mode, int ibf16, const RowArgs& a, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  if constexpr (kHasVar) {
+  if constexpr (kHasVar && !kWide) {
     using P1 = Plan<GL1, GL2, -1, 1>;
     return ibf16 ? launch_t<P1, uint16_t>(mode, a, s) : launch_t<P1, float>(mode, a, s);
   } else {
-    using P0 = Plan<GL1, GL2>;
-    return ibf16 ? launch_t<P0, uint16_t>(mode, a, s) : launch_t<P0, float>(mode, a, s);
+    return TM_CAT(row_launch, GL1, GL2)(mode, ibf16, a, stream);
   }
 }
 

@@ -4,6 +4,7 @@
 #pragma once
 #include "fft_core.hpp"
 #include "lbfgs.hpp"
+#include "wide_fft.hpp"
 
 namespace tmk {
 
@@ -241,15 +242,122 @@ __device__ __forceinline__ double row_reduce64(double v, double* red, int tid) {
   }
 }
 
+// Where a thread's values sit: element indices at the first pass, natural
+// frequency indices at the last.
+template <class PL, bool W = PL::WIDE>
+struct Where {
+  using L0 = Layout0<PL>;
+  using LL = LayoutL<PL>;
+  int b0[L0::NB], kb[LL::NB];
+  __device__ __forceinline__ explicit Where(int ltid) {
+#pragma unroll
+    for (int j = 0; j < L0::NB; ++j) b0[j] = L0::base(ltid, j);
+#pragma unroll
+    for (int j = 0; j < LL::NB; ++j) kb[j] = LL::kbase(ltid, j);
+  }
+  __device__ __forceinline__ int elem_l(int i) const { return b0[i / L0::R]; }
+  __device__ __forceinline__ int elem_r(int i) const { return (i % L0::R) * L0::HS; }
+  __device__ __forceinline__ int freq_l(int i) const { return kb[i / LL::R]; }
+  __device__ __forceinline__ int freq_r(int i) const { return (i % LL::R) * LL::KS; }
+};
+template <class PL>
+struct Where<PL, true> {
+  int b0, kb;
+  __device__ __forceinline__ explicit Where(int ltid)
+      : b0(PL::template thr_base<0, PL::ELEM>(ltid)), kb(PL::template thr_base<PL::NP - 1, PL::FREQ>(ltid)) {}
+  __device__ __forceinline__ int elem_l(int) const { return b0; }
+  __device__ __forceinline__ int elem_r(int i) const { return PL::template reg_off<0, PL::ELEM>(i); }
+  __device__ __forceinline__ int freq_l(int) const { return kb; }
+  __device__ __forceinline__ int freq_r(int i) const { return PL::template reg_off<PL::NP - 1, PL::FREQ>(i); }
+};
+
+// Access to value `lane + reg` of an array at p, `reg` a constant of the
+// register. With 32 values per thread p is the same in every lane and the
+// access is a buffer one: one 32-bit offset per lane, the register's part in
+// the instruction or a scalar. As global accesses the compiler kept 32 64-bit
+// addresses per array in registers across the mask loop (120 to 200 spilled).
+typedef unsigned tm_v2u __attribute__((ext_vector_type(2)));
+template <typename V>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const V* p) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)wave_uniform((V*)p), 0, 0xffffffff, 0x00020000);
+}
+template <int SZ>
+__device__ __forceinline__ void split_off(int lane, int reg, int& v, int& s) {
+  const int b = reg * SZ;
+  v = lane * SZ + (b & 4095);  // the low part goes into the instruction's offset
+  s = b & ~4095;
+}
+template <bool W>
+__device__ __forceinline__ cx<float> ld(const cx<float>* p, int lane, int reg) {
+  if constexpr (W) {
+    int v, s;
+    split_off<8>(lane, reg, v, s);
+    const tm_v2u u = __builtin_amdgcn_raw_buffer_load_b64(rsrc_of(p), v, s, 0);
+    return cx<float>{__uint_as_float(u.x), __uint_as_float(u.y)};
+  } else {
+    return gload(p + lane + reg);
+  }
+}
+constexpr int NT = 2;  // non-temporal: large outputs that this kernel does not read
+template <bool W, int AUX = 0>
+__device__ __forceinline__ void st(cx<float>* p, int lane, int reg, cx<float> c) {
+  if constexpr (W) {
+    int v, s;
+    split_off<8>(lane, reg, v, s);
+    __builtin_amdgcn_raw_buffer_store_b64(tm_v2u{__float_as_uint(c.x), __float_as_uint(c.y)}, rsrc_of(p), v, s, AUX);
+  } else {
+    gstore(p + lane + reg, c);
+  }
+}
+template <bool W, typename IT>
+__device__ __forceinline__ float ld_I(const IT* p, int lane, int reg) {
+  if constexpr (W) {
+    int v, s;
+    split_off<sizeof(IT)>(lane, reg, v, s);
+    if constexpr (sizeof(IT) == 2) return bf16_to_f(__builtin_amdgcn_raw_buffer_load_b16(rsrc_of(p), v, s, 0));
+    else return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc_of(p), v, s, 0));
+  } else {
+    return load_I<IT>(p, (size_t)(lane + reg));
+  }
+}
+template <bool W>
+__device__ __forceinline__ void st_f(float* p, int lane, int reg, float f) {
+  if constexpr (W) {
+    int v, s;
+    split_off<4>(lane, reg, v, s);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f), rsrc_of(p), v, s, 0);
+  } else {
+    gw(p)[lane + reg] = f;
+  }
+}
+template <bool W>
+__device__ __forceinline__ void st_h(uint16_t* p, int lane, int reg, uint16_t h) {
+  if constexpr (W) {
+    int v, s;
+    split_off<2>(lane, reg, v, s);
+    __builtin_amdgcn_raw_buffer_store_b16(h, rsrc_of(p), v, s, 0);
+  } else {
+    gw(p)[lane + reg] = h;
+  }
+}
+
+template <class PL, typename T, bool W = PL::WIDE>
+struct FftOf { using type = LineFft<PL, T>; };
+template <class PL, typename T>
+struct FftOf<PL, T, true> { using type = WideFft<PL, T>; };
+
 // Shape of one workgroup of WGT threads (default: one row of T threads, at
-// least 256 threads).
-template <class PL, int WGT = ((PL::T >= 256) ? PL::T : 256)>
+// least 256 threads; with 32 values per thread at least one wave).
+template <class PL>
+constexpr int default_wg() {
+  constexpr int least = PL::WIDE ? 64 : 256;
+  return PL::T >= least ? PL::T : least;
+}
+template <class PL, int WGT = default_wg<PL>()>
 struct Launch {
   static constexpr int WG = WGT;
   static constexpr int RPW = WG / PL::T;  // rows per workgroup
-  // double-buffered LDS exchange when two copies of the rows fit in 160 KiB
-  static constexpr bool DB = 2 * RPW * PL::LDS_ROW * 8 <= 160 * 1024 - 4096;
-  static constexpr int LDS_ELEMS = (DB ? 2 : 1) * RPW * PL::LDS_ROW;
+  static constexpr int LDS_ELEMS = RPW * PL::LDS_ROW + PL::LDS_TW;
   static constexpr int RED_FLOATS = (WG / 64 + 1) * NSUM * 2;
 };
 
@@ -271,10 +379,6 @@ __device__ __forceinline__ float wtab_eval(const RowArgs& a, float x) {
 // SUMS: accumulate the per-row monitoring sums (compensated) and write them;
 // without it the kernel skips that work (used on iterations whose sums are
 // not read).
-#ifndef TM_MINW
-#define TM_MINW 1
-#endif
-
 // Body of the fused kernel for the rows [blk * RPW, (blk + 1) * RPW) of one
 // problem, run by a workgroup of WGT threads with LDS at lds_all (at least
 // Launch<PL, WGT>::LDS_ELEMS elements) and red (RED_FLOATS floats).
@@ -294,7 +398,6 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
   using C = cx<T>;
   using LC = Launch<PL, WGT>;
   constexpr int E = PL::E, N = PL::N, WG = LC::WG, RPW = LC::RPW;
-  constexpr int NBUF = LC::DB ? 2 : 1;
 
   const int tid = threadIdx.x;
   const int rloc = tid / PL::T;
@@ -302,35 +405,46 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
   const int row = blk * RPW + rloc;
   const bool valid = row < a.P;
   const size_t prow = valid ? (size_t)row : 0;
-  Xbuf<T> xb{lds_all + rloc * PL::LDS_ROW, (NBUF == 2) ? RPW * PL::LDS_ROW : 0, 0};
-  Tw<T> tw{a.tw32 + (PL::N1 - 1), a.tw32 + (PL::N2 - 1)};
-
-  using L0 = Layout0<PL>;
-  using LL = LayoutL<PL>;
-  int b0[L0::NB];  // pass-0 butterfly bases (natural element index)
-#pragma unroll
-  for (int j = 0; j < L0::NB; ++j) b0[j] = L0::base(ltid, j);
-  int kb[LL::NB];  // last-pass butterfly spectrum bases
-#pragma unroll
-  for (int j = 0; j < LL::NB; ++j) kb[j] = LL::kbase(ltid, j);
-#define E0(i) (b0[(i) / L0::R] + ((i) % L0::R) * L0::HS)
-#define KL(i) (kb[(i) / LL::R] + ((i) % LL::R) * LL::KS)
+  const typename FftOf<PL, T>::type fft(lds_all + rloc * PL::LDS_ROW, lds_all + RPW * PL::LDS_ROW, ltid,
+                                      a.tw32 + (PL::N1 - 1),
+                                      a.tw32 + (PL::N2 - 1));
+  const Where<PL> at(ltid);
+  // Arrays of the row: with 32 values per thread their bases are those of the
+  // workgroup's first row (the same in every lane; an invalid row reads that
+  // one) and the row's distance goes into the lane offsets.
+  constexpr bool W = PL::WIDE;
+  const size_t brow = W ? (size_t)blk * RPW : prow;
+  const int rl = (W && RPW > 1 && valid) ? rloc : 0;
+  const int rn = rl * N, rk = rl * a.K * N;
+#define LD_ROW(p, i) ld<W>(p, rn + at.elem_l(i), at.elem_r(i))
+#define ST_ROW(p, i, c) st<W>(p, rn + at.elem_l(i), at.elem_r(i), c)
+#define LD_MASK(i) ld<W>(mk, at.elem_l(i), at.elem_r(i))
+#define LD_I(i) ld_I<W, IT>(Im, rk + at.freq_l(i), at.freq_r(i))
 
   // The row t is held in registers across the mask loop (re-reading it per
-  // mask from cache measured slower); d (M_LS) is re-read per mask.
+  // mask from cache measured slower). The mixed-axis plan's 128 registers do not
+  // hold it beside the accumulator and the transform: half of it stays and the
+  // other half is read again for each mask (all of it re-read: 4 MB of rows per
+  // XCD, which its L2 does not keep, 1.26 GB from HBM per Lanczos launch at
+  // 2286 x 8192 against 0.6). The cyclic sweep has no accumulator and keeps it
+  // all. d (M_LS) is re-read per mask.
+  constexpr int KEEP = (!PL::WIDE || MODE == M_ERC) ? E : (MODE == M_LS || MODE == M_ALS || MODE == M_WBACK) ? 4 : PL::WAVES < 4 && !OOL ? 12 : 8;
+  constexpr bool KEEP_T = KEEP == E;
   C g[E], x[E];
-  const C* trow = a.tin + prow * N;
-  const C* drow = a.din + prow * N;
+  const C* trow = a.tin + brow * N;
+  const C* drow = a.din + brow * N;
   C treg[E];
   if constexpr (MODE != M_ADJ && MODE != M_BACKPROP) {
 #pragma unroll
-    for (int i = 0; i < E; ++i) treg[i] = gload(trow + E0(i));
+    for (int i = 0; i < KEEP; ++i) treg[i] = LD_ROW(trow, i);
   }
   float lz_mean0 = 1.f;  // the row's mean intensity when this (first Lanczos) step forms it
   if constexpr (MODE == M_LANCZOS) {
     if (a.lz_sum) {
       // seed norm and intensity sum in FP64; the intensities read along the
       // row (consecutive threads, consecutive values), mask by mask
+#pragma unroll
+      for (int i = KEEP; i < E; ++i) treg[i] = LD_ROW(trow, i);
       double sn = 0.0, si = 0.0;
 #pragma unroll
       for (int i = 0; i < E; ++i)
@@ -351,7 +465,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
       if (valid) {
         C* t1 = const_cast<C*>(trow);
 #pragma unroll
-        for (int i = 0; i < E; ++i) gstore(t1 + E0(i), treg[i]);
+        for (int i = 0; i < E; ++i) ST_ROW(t1, i, treg[i]);
         if (ltid == 0) {
           gw(a.lz_sum)[prow] = si;
           gw(a.lz_mean)[prow] = lz_mean0;
@@ -368,40 +482,45 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
       const int head = (int)sc[0], count = (int)sc[1];
       const double* coef = sc + 4 + 2 * R * R;
       const float cg = (float)coef[0];
-      C dv[E];
+      const C *lbS = a.lb_S + brow * R * N, *lbY = a.lb_Y + brow * R * N;
+      C* dout = a.lb_d + brow * N;
+      constexpr int CH = PL::WIDE ? 8 : E;  // values at a time (their loads' registers)
 #pragma unroll
-      for (int i = 0; i < E; ++i) {
-        const C gv = gload(a.lb_g + prow * N + E0(i));
-        dv[i] = C{cg * gv.x, cg * gv.y};
-      }
-      for (int j = 0; j < count; j += 2) {
-        const bool two = j + 1 < count;
-        const size_t s0 = ((size_t)prow * R + (head - count + j + 2 * R) % R) * N;
-        const size_t s1 = ((size_t)prow * R + (head - count + j + 1 + 2 * R) % R) * N;
-        C sv0[E], yv0[E], sv1[E], yv1[E];
+      for (int c = 0; c < E; c += CH) {
+        C dv[CH];
 #pragma unroll
-        for (int i = 0; i < E; ++i) {
-          sv0[i] = gload(a.lb_S + s0 + E0(i));
-          yv0[i] = gload(a.lb_Y + s0 + E0(i));
-          sv1[i] = two ? gload(a.lb_S + s1 + E0(i)) : C{0.f, 0.f};
-          yv1[i] = two ? gload(a.lb_Y + s1 + E0(i)) : C{0.f, 0.f};
+        for (int i = 0; i < CH; ++i) {
+          const C gv = LD_ROW(a.lb_g + brow * N, c + i);
+          dv[i] = C{cg * gv.x, cg * gv.y};
         }
-        const float cs0 = (float)coef[1 + j], cy0 = (float)coef[1 + R + j];
-        const float cs1 = two ? (float)coef[2 + j] : 0.f, cy1 = two ? (float)coef[2 + R + j] : 0.f;
+        for (int j = 0; j < count; j += 2) {
+          const bool two = j + 1 < count;
+          const int s0 = (rl * R + (head - count + j + 2 * R) % R) * N;
+          const int s1 = (rl * R + (head - count + j + 1 + 2 * R) % R) * N;
+          C sv0[CH], yv0[CH], sv1[CH], yv1[CH];
 #pragma unroll
-        for (int i = 0; i < E; ++i) {
-          dv[i].x = fmadd(cy0, yv0[i].x, fmadd(cs0, sv0[i].x, dv[i].x));
-          dv[i].y = fmadd(cy0, yv0[i].y, fmadd(cs0, sv0[i].y, dv[i].y));
-          if (two) {
-            dv[i].x = fmadd(cy1, yv1[i].x, fmadd(cs1, sv1[i].x, dv[i].x));
-            dv[i].y = fmadd(cy1, yv1[i].y, fmadd(cs1, sv1[i].y, dv[i].y));
+          for (int i = 0; i < CH; ++i) {
+            sv0[i] = ld<W>(lbS, s0 + at.elem_l(c + i), at.elem_r(c + i));
+            yv0[i] = ld<W>(lbY, s0 + at.elem_l(c + i), at.elem_r(c + i));
+            sv1[i] = two ? ld<W>(lbS, s1 + at.elem_l(c + i), at.elem_r(c + i)) : C{0.f, 0.f};
+            yv1[i] = two ? ld<W>(lbY, s1 + at.elem_l(c + i), at.elem_r(c + i)) : C{0.f, 0.f};
+          }
+          const float cs0 = (float)coef[1 + j], cy0 = (float)coef[1 + R + j];
+          const float cs1 = two ? (float)coef[2 + j] : 0.f, cy1 = two ? (float)coef[2 + R + j] : 0.f;
+#pragma unroll
+          for (int i = 0; i < CH; ++i) {
+            dv[i].x = fmadd(cy0, yv0[i].x, fmadd(cs0, sv0[i].x, dv[i].x));
+            dv[i].y = fmadd(cy0, yv0[i].y, fmadd(cs0, sv0[i].y, dv[i].y));
+            if (two) {
+              dv[i].x = fmadd(cy1, yv1[i].x, fmadd(cs1, sv1[i].x, dv[i].x));
+              dv[i].y = fmadd(cy1, yv1[i].y, fmadd(cs1, sv1[i].y, dv[i].y));
+            }
           }
         }
-      }
-      C* dout = a.lb_d + prow * N;
-      if (valid) {
+        if (valid) {
 #pragma unroll
-        for (int i = 0; i < E; ++i) gstore(dout + E0(i), dv[i]);
+          for (int i = 0; i < CH; ++i) ST_ROW(dout, c + i, dv[i]);
+        }
       }
       drow = dout;
     }
@@ -413,9 +532,9 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
       // store precedes the FFTs (the twiddle tables stay scalar loads).
       const float b = a.er_beta;
 #pragma unroll
-      for (int i = 0; i < E; ++i) {
-        C tp = gload(drow + E0(i));
-        treg[i] = C{treg[i].x + b * (treg[i].x - tp.x), treg[i].y + b * (treg[i].y - tp.y)};
+      for (int i = 0; i < KEEP; ++i) {
+        C tp = LD_ROW(drow, i);
+        treg[i] = axpy(b, treg[i] - tp, treg[i]);
       }
     }
   }
@@ -434,11 +553,11 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
       // one basis row at a time (groups of rows in flight measured no faster: one
       // workgroup per CU, so these loads do not overlap the transforms either way)
       for (int j = 1; j < a.lz_k; ++j) {
-        const C* vr = a.lz_basis + (size_t)(j - 1) * a.lz_rs + prow * N;
+        const C* vr = a.lz_basis + (size_t)(j - 1) * a.lz_rs + brow * N;
         const double w = yp[j];
         C v[E];
 #pragma unroll
-        for (int i = 0; i < E; ++i) v[i] = gload(vr + E0(i));
+        for (int i = 0; i < E; ++i) v[i] = LD_ROW(vr, i);
 #pragma unroll
         for (int i = 0; i < E; ++i) {
           ax[i] += w * v[i].x;
@@ -449,7 +568,22 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
       for (int i = 0; i < E; ++i) treg[i] = C{(float)ax[i], (float)ay[i]};
     }
   }
-#define TROW(i) treg[i]
+  // Value i of the row whose transform is taken. `again` is 0, set anew for each
+  // mask where the compiler cannot see it: it would otherwise move the loads
+  // out of the mask loop and spill them.
+  int again = 0;
+  auto row_at = [&](int i) -> C {
+    if (i < KEEP) return treg[i];
+    C v = LD_ROW(trow + again, i);
+    if constexpr (MODE == M_ER) {
+      if (a.er_beta != 0.f) {
+        const C tp = LD_ROW(drow + again, i);
+        v = axpy(a.er_beta, v - tp, v);
+      }
+    }
+    return v;
+  };
+#define TROW(i) row_at(i)
 #pragma unroll
   for (int i = 0; i < E; ++i) g[i] = C{0.f, 0.f};
 
@@ -473,25 +607,37 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
   // 2286 x 8192). The ER and gradient steps load the mask twice and the
   // intensities after the transform: the same changes measured slower there
   // (cyclic ER 0.357 -> 0.376 and 0.413 ms).
-  constexpr bool PF = MODE == M_SPEC || MODE == M_LANCZOS || MODE == M_LANCZOS_T || MODE == M_WAPPLY;
-  float icur[PF ? E : 1];
-  C mv[PF ? E : 1];     // the mask's values, kept for the conjugate multiply
+  constexpr bool PF = !PL::WIDE && (MODE == M_SPEC || MODE == M_LANCZOS || MODE == M_LANCZOS_T || MODE == M_WAPPLY);
+  // Mixed-axis plan: at its 128 registers the compiler waits for each load in
+  // turn (Lanczos step 419 us at 2286 x 8192, 294 in groups), so the loads are issued in
+  // groups: the mask's and the row's values, then the intensities (loads return
+  // in order: these stay in flight during the forward transform), the mask's
+  // values for the conjugate multiply half during the inverse transform's last
+  // pass and half after it.
+  constexpr bool WI = W && (MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_SPEC || MODE == M_LANCZOS ||
+                            MODE == M_AGRAD || MODE == M_LANCZOS_T || MODE == M_WAPPLY);
+  constexpr bool WM = WI || (W && (MODE == M_ADJ || MODE == M_BACKPROP || MODE == M_FILT || MODE == M_WBACK));
+  constexpr int MH = KEEP_T ? E : E / 2;  // of them loaded during that pass
+  float icur[PF || WI ? E : 1];
+  C mv[PF || WM ? E : 1];  // the mask's values for the conjugate multiply
   C mnext[PF ? E : 1];  // the next mask's values, loaded during the last inverse pass
   if constexpr (PF) {
 #pragma unroll
-    for (int i = 0; i < E; ++i) mnext[i] = gload(a.masks + E0(i));
+    for (int i = 0; i < E; ++i) mnext[i] = ld<W>(a.masks, at.elem_l(i), at.elem_r(i));
   }
   for (int m = 0; m < a.K; ++m) {
+    if constexpr (!KEEP_T) again = hidden_zero();
     const C* mk = a.masks + (size_t)m * N;
-    const size_t mbase = (prow * a.K + m) * (size_t)N;
+    const size_t mbase = (brow * a.K + m) * (size_t)N;
+    const IT* Im = (const IT*)a.I + mbase;
     if constexpr (MODE == M_ADJ || MODE == M_BACKPROP) {
       // spectrum arrives in natural order; place it at the digit-reversed slots
 #pragma unroll
       for (int i = 0; i < E; ++i) {
-        int k = KL(i);
-        if constexpr (MODE == M_ADJ) x[i] = gload(a.yin + mbase + k);
-        else x[i] = C{sqrtf(fmaxf(load_I<IT>(a.I, mbase + k), 0.f)), 0.f};
+        if constexpr (MODE == M_ADJ) x[i] = ld<W>(a.yin + mbase, rk + at.freq_l(i), at.freq_r(i));
+        else x[i] = C{sqrtf(fmaxf(LD_I(i), 0.f)), 0.f};
       }
+      if (m > 0) fft.fence();
     } else {
       if constexpr (PF) {
         // the intensity loads go out after the (earlier) mask loads, so the
@@ -501,34 +647,56 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
         for (int i = 0; i < E; ++i) mv[i] = mnext[i];
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < E; ++i) icur[i] = load_I<IT>(a.I, mbase + KL(i));
+        for (int i = 0; i < E; ++i) icur[i] = LD_I(i);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < E; ++i) x[i] = cmul(TROW(i), mv[i]);
+      } else if constexpr (W) {
+        C tv[E - KEEP + 1];
+#pragma unroll
+        for (int i = KEEP; i < E; ++i) {
+          x[i] = LD_MASK(i);
+          tv[i - KEEP] = row_at(i);
+        }
+#pragma unroll
+        for (int i = 0; i < KEEP; ++i) x[i] = LD_MASK(i);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (WI) {
+#pragma unroll
+          for (int i = 0; i < E; ++i) icur[i] = LD_I(i);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = KEEP; i < E; ++i) x[i] = cmul(tv[i - KEEP], x[i]);
+#pragma unroll
+        for (int i = 0; i < KEEP; ++i) x[i] = cmul(treg[i], x[i]);
       } else if constexpr (MODE == M_ERC && OOL) {
         C mvals[E];
 #pragma unroll
-        for (int i = 0; i < E; ++i) mvals[i] = gload(mk + E0(i));
+        for (int i = 0; i < E; ++i) mvals[i] = LD_MASK(i);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < E; ++i) x[i] = cmul(TROW(i), mvals[i]);
       } else {
 #pragma unroll
-        for (int i = 0; i < E; ++i) x[i] = cmul(TROW(i), gload(mk + E0(i)));
+        for (int i = 0; i < E; ++i) x[i] = cmul(TROW(i), LD_MASK(i));
       }
-      fft_forward<PL, T>(x, xb, ltid, tw);
+      if constexpr (MODE == M_FWD_FIELD || MODE == M_FWD_INT || MODE == M_LS || MODE == M_ALS) {
+        if (m > 0) fft.fence();
+      }
+      fft.forward(x);
     }
 
     if constexpr (MODE == M_FWD_FIELD || MODE == M_FWD_INT) {
       if (valid) {
 #pragma unroll
         for (int i = 0; i < E; ++i) {
-          int k = KL(i);
-          if constexpr (MODE == M_FWD_FIELD) gstore((C*)a.yout + mbase + k, x[i]);
+          const int kl = rk + at.freq_l(i), kr = at.freq_r(i);
+          if constexpr (MODE == M_FWD_FIELD) st<W, NT>((C*)a.yout + mbase, kl, kr, x[i]);
           else {
             float v = norm2(x[i]);
-            if (a.out_bf16) gw((uint16_t*)a.yout)[mbase + k] = f_to_bf16(v);
-            else gw((float*)a.yout)[mbase + k] = v;
+            if (a.out_bf16) st_h<W>((uint16_t*)a.yout + mbase, kl, kr, f_to_bf16(v));
+            else st_f<W>((float*)a.yout + mbase, kl, kr, v);
           }
         }
       }
@@ -539,18 +707,35 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
 #pragma unroll
       for (int i = 0; i < E; ++i) y[i] = x[i];
 #pragma unroll
-      for (int i = 0; i < E; ++i) x[i] = cmul(gload(drow + E0(i)), gload(mk + E0(i)));
-      fft_forward<PL, T>(x, xb, ltid, tw);
+      for (int i = 0; i < E; ++i) x[i] = LD_ROW(drow, i);
+      C dm[W ? E : 1];
+      if constexpr (W) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) dm[i] = LD_MASK(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int i = 0; i < E; ++i) {
-        int k = KL(i);
-        const float amp = hw_sqrt(fmaxf(load_I<IT>(a.I, mbase + k), 0.f));
+        if constexpr (W) x[i] = cmul(x[i], dm[i]);
+        else x[i] = cmul(x[i], LD_MASK(i));
+      }
+      float ivs[W ? E : 1];
+      if constexpr (W) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) ivs[i] = LD_I(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      fft.fence();
+      fft.forward(x);
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        const float amp = hw_sqrt(fmaxf(W ? ivs[i] : LD_I(i), 0.f));
         const float r0 = amp - hw_sqrt(norm2(y[i]));
         acc[0].add(r0 * r0);
 #pragma unroll
         for (int j = 0; j < AMP_TRIALS; ++j) {
           const float st = ldexpf(1.f, j - 3);
-          const C w = C{y[i].x + st * x[i].x, y[i].y + st * x[i].y};
+          const C w = axpy(st, x[i], y[i]);
           const float r = amp - hw_sqrt(norm2(w));
           acc[1 + j].add(r * r);
         }
@@ -561,14 +746,31 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
 #pragma unroll
       for (int i = 0; i < E; ++i) y[i] = x[i];
 #pragma unroll
-      for (int i = 0; i < E; ++i) x[i] = cmul(gload(drow + E0(i)), gload(mk + E0(i)));
-      fft_forward<PL, T>(x, xb, ltid, tw);
+      for (int i = 0; i < E; ++i) x[i] = LD_ROW(drow, i);
+      C dm[W ? E : 1];
+      if constexpr (W) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) dm[i] = LD_MASK(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int i = 0; i < E; ++i) {
-        int k = KL(i);
-        float iv = load_I<IT>(a.I, mbase + k);
+        if constexpr (W) x[i] = cmul(x[i], dm[i]);
+        else x[i] = cmul(x[i], LD_MASK(i));
+      }
+      float ivs[W ? E : 1];
+      if constexpr (W) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) ivs[i] = LD_I(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      fft.fence();
+      fft.forward(x);
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        float iv = W ? ivs[i] : LD_I(i);
         float r = iv - norm2(y[i]);
-        float b = y[i].x * x[i].x + y[i].y * x[i].y;
+        float b = rdot(y[i], x[i]);
         float c = norm2(x[i]);
         acc[0].add(r * r);
         acc[1].add(r * b);
@@ -582,7 +784,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
       if constexpr (MODE == M_FILT) {
         // multiply the spectrum by the filter (read at each slot's natural frequency)
 #pragma unroll
-        for (int i = 0; i < E; ++i) x[i] = cmul(x[i], gload(a.yin + KL(i)));
+        for (int i = 0; i < E; ++i) x[i] = cmul(x[i], ld<W>(a.yin, at.freq_l(i), at.freq_r(i)));
       }
       if constexpr (MODE == M_WBACK) {
         // second transform z = A d of this mask; gw = Re(conj(z) y) at each
@@ -591,30 +793,41 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
 #pragma unroll
         for (int i = 0; i < E; ++i) y[i] = x[i];
 #pragma unroll
-        for (int i = 0; i < E; ++i) x[i] = cmul(gload(drow + E0(i)), gload(mk + E0(i)));
-        fft_forward<PL, T>(x, xb, ltid, tw);
+        for (int i = 0; i < E; ++i) x[i] = LD_ROW(drow, i);
+      C dm[W ? E : 1];
+      if constexpr (W) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) dm[i] = LD_MASK(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        if constexpr (W) x[i] = cmul(x[i], dm[i]);
+        else x[i] = cmul(x[i], LD_MASK(i));
+      }
+        fft.fence();
+        fft.forward(x);
 #pragma unroll
         for (int i = 0; i < E; ++i) {
-          const int k = KL(i);
-          const float w = wtab_eval(a, load_I<IT>(a.I, mbase + k) * inv_mean);
-          if (valid) gw((float*)a.yout)[mbase + k] = y[i].x * x[i].x + y[i].y * x[i].y;
+          const float w = wtab_eval(a, LD_I(i) * inv_mean);
+          if (valid) st_f<W>((float*)a.yout + mbase, rk + at.freq_l(i), at.freq_r(i), rdot(y[i], x[i]));
           x[i] = scl(x[i], w);
         }
       }
       if constexpr (MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_SPEC || MODE == M_LANCZOS ||
                     MODE == M_AGRAD || MODE == M_LANCZOS_T || MODE == M_WAPPLY) {
-        float ierc[MODE == M_ERC && OOL ? E : 1];  // the intensities loaded together (OOL)
-        if constexpr (MODE == M_ERC && OOL) {
+        float ierc[MODE == M_ERC && OOL && !W ? E : 1];  // the intensities loaded together (OOL)
+        if constexpr (MODE == M_ERC && OOL && !W) {
 #pragma unroll
-          for (int i = 0; i < E; ++i) ierc[i] = load_I<IT>(a.I, mbase + KL(i));
+          for (int i = 0; i < E; ++i) ierc[i] = LD_I(i);
           __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int i = 0; i < E; ++i) {
           float iv;
-          if constexpr (PF) iv = icur[i];
-          else if constexpr (MODE == M_ERC && OOL) iv = ierc[i];
-          else iv = load_I<IT>(a.I, mbase + KL(i));
+          if constexpr (PF || WI) iv = icur[i];
+          else if constexpr (MODE == M_ERC && OOL && !W) iv = ierc[i];
+          else iv = LD_I(i);
           float n = norm2(x[i]);
           if constexpr (MODE == M_ER || MODE == M_ERC) {
             // keep the measured amplitude, keep the phase (y/|y| := 1 at y = 0)
@@ -655,33 +868,48 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
       if constexpr (PF) {
         const C* mk1 = mk + N;
         const bool more = m + 1 < a.K;
-        fft_inverse<PL, T>(x, xb, ltid, tw, [&]() {
+        fft.inverse(x, [&]() {
           if (more) {
 #pragma unroll
-            for (int i = 0; i < E; ++i) mnext[i] = gload(mk1 + E0(i));
+            for (int i = 0; i < E; ++i) mnext[i] = ld<W>(mk1, at.elem_l(i), at.elem_r(i));
           }
         });
+      } else if constexpr (WM) {
+        fft.inverse(x, [&]() {
+#pragma unroll
+          for (int i = 0; i < MH; ++i) mv[i] = LD_MASK(i);
+          __builtin_amdgcn_sched_barrier(0);
+        });
       } else {
-        fft_inverse<PL, T>(x, xb, ltid, tw);
+        fft.inverse(x);
       }
       if constexpr (MODE == M_ERC) {
         // this mask's projection replaces the row before the next mask
         const float inv_n = 1.f / (float)N;
-        if constexpr (OOL) {
+        if constexpr (WM) {
 #pragma unroll
-          for (int i = 0; i < E; ++i) g[i] = gload(mk + E0(i));  // g is free in this mode: the mask values
+          for (int i = 0; i < E; ++i) treg[i] = scl(cmulc(x[i], mv[i]), inv_n);
+        } else if constexpr (OOL) {
+#pragma unroll
+          for (int i = 0; i < E; ++i) g[i] = LD_MASK(i);  // g is free in this mode: the mask values
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int i = 0; i < E; ++i) treg[i] = scl(cmulc(x[i], g[i]), inv_n);
         } else {
 #pragma unroll
-          for (int i = 0; i < E; ++i) treg[i] = scl(cmulc(x[i], gload(mk + E0(i))), inv_n);
+          for (int i = 0; i < E; ++i) treg[i] = scl(cmulc(x[i], LD_MASK(i)), inv_n);
         }
       } else {
 #pragma unroll
         for (int i = 0; i < E; ++i) {
-          if constexpr (PF) g[i] = g[i] + cmulc(x[i], mv[i]);
-          else g[i] = g[i] + cmulc(x[i], gload(mk + E0(i)));
+          if (WM && i == MH) {  // x of the first half is free for the others' loads
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = MH; k < E; ++k) mv[k] = LD_MASK(k);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if constexpr (PF || WM) g[i] = g[i] + cmulc(x[i], mv[i]);
+          else g[i] = g[i] + cmulc(x[i], LD_MASK(i));
         }
       }
     }
@@ -701,20 +929,28 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
     // alpha = Re <v, M v>; x = M v - alpha v - beta v_prev with beta = ||x|| of the
     // previous step (0 at the first, where there is no v_prev); v_next = x / ||x||.
     // ||x|| is summed from x itself (a second reduction), not expanded.
+    if constexpr (!KEEP_T) {
+#pragma unroll
+      for (int i = KEEP; i < E; ++i) treg[i] = row_at(i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     KSum q[1];
     q[0] = KSum{0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < E; ++i) q[0].add(TROW(i).x * g[i].x + TROW(i).y * g[i].y);
+    for (int i = 0; i < E; ++i) q[0].add(rdot(treg[i], g[i]));
     float o1[1];
     row_reduce<PL::T, WG, 1>(q, red, tid, o1);
     const float al = o1[0];
     if (a.lz_bprev) {
       const float bp = valid ? gc(a.lz_bprev)[prow * 2 + 1] : 0.f;
 #pragma unroll
-      for (int i = 0; i < E; ++i) g[i] = g[i] - scl(TROW(i), al) - scl(gload(drow + E0(i)), bp);
+      for (int i = 0; i < E; ++i) x[i] = LD_ROW(drow, i);
+      if constexpr (W) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < E; ++i) g[i] = axpy(-bp, x[i], axpy(-al, treg[i], g[i]));
     } else {
 #pragma unroll
-      for (int i = 0; i < E; ++i) g[i] = g[i] - scl(TROW(i), al);
+      for (int i = 0; i < E; ++i) g[i] = axpy(-al, treg[i], g[i]);
     }
     q[0] = KSum{0.f, 0.f};
 #pragma unroll
@@ -725,7 +961,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
     const float inv = nrm > 0.f ? 1.f / nrm : 0.f;
     if (valid) {
 #pragma unroll
-      for (int i = 0; i < E; ++i) gstore(a.tout + prow * N + E0(i), scl(g[i], inv));
+      for (int i = 0; i < E; ++i) ST_ROW(a.tout + brow * N, i, scl(g[i], inv));
       if (ltid == 0) {
         gw(a.lz_out)[prow * 2 + 0] = al;
         gw(a.lz_out)[prow * 2 + 1] = nrm;
@@ -743,19 +979,23 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
     const float sp = valid ? gc(a.vscale)[prow] : 0.f;
     C vp[E];
 #pragma unroll
-    for (int i = 0; i < E; ++i) vp[i] = gload(drow + E0(i));
+    for (int i = 0; i < E; ++i) {
+      vp[i] = LD_ROW(drow, i);
+      if (i >= KEEP) treg[i] = row_at(i);
+    }
+    if constexpr (W) __builtin_amdgcn_sched_barrier(0);
     KSum q[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) q[i] = KSum{0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-      C ti = TROW(i);
-      q[0].add(ti.x * g[i].x + ti.y * g[i].y);
+      C ti = treg[i];
+      q[0].add(rdot(ti, g[i]));
       q[1].add(norm2(g[i]));
-      q[2].add(vp[i].x * g[i].x + vp[i].y * g[i].y);
+      q[2].add(rdot(vp[i], g[i]));
       q[3].add(norm2(vp[i]));
       q[4].add(norm2(ti));
-      q[5].add(vp[i].x * ti.x + vp[i].y * ti.y);
+      q[5].add(rdot(vp[i], ti));
     }
     float out[6];
     row_reduce<PL::T, WG, 6>(q, red, tid, out);
@@ -770,7 +1010,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
     if (valid) {
 #pragma unroll
       for (int i = 0; i < E; ++i)
-        gstore(a.tout + prow * N + E0(i), scl(g[i] - scl(TROW(i), sig) - scl(vp[i], bs), inv));
+        ST_ROW(a.tout + brow * N, i, scl(axpy(-bs, vp[i], axpy(-sig, treg[i], g[i])), inv));
       if (ltid == 0) {
         gw(a.vscale)[prow] = inv;
         if (a.sums) gw(a.sums)[prow * NSUM + 0] = lam;
@@ -785,7 +1025,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
     row_reduce<PL::T, WG, 1>(q, red, tid, o1);
     if (valid) {
 #pragma unroll
-      for (int i = 0; i < E; ++i) gstore(a.tout + prow * N + E0(i), g[i]);
+      for (int i = 0; i < E; ++i) ST_ROW(a.tout + brow * N, i, g[i]);
       if (ltid == 0) gw(a.sums)[prow * NSUM + 0] = o1[0];
     }
   } else {
@@ -795,10 +1035,10 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
     if (valid) {
       if constexpr (MODE == M_ERC) {
 #pragma unroll
-        for (int i = 0; i < E; ++i) gstore(a.tout + prow * N + E0(i), treg[i]);
+        for (int i = 0; i < E; ++i) ST_ROW(a.tout + brow * N, i, treg[i]);
       } else {
 #pragma unroll
-        for (int i = 0; i < E; ++i) gstore(a.tout + prow * N + E0(i), scl(g[i], scale));
+        for (int i = 0; i < E; ++i) ST_ROW(a.tout + brow * N, i, scl(g[i], scale));
       }
     }
     if constexpr ((MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_AGRAD) && SUMS) {
@@ -816,8 +1056,11 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
   }
 }
 
+// Registers for PL::WAVES waves per SIMD: the mixed-axis plan fits them by
+// design; the one-axis plans spill when the compiler aims at more than two
+// (gradient at 2286 x 2048: 131 us against 88).
 template <class PL, int MODE, typename IT, bool SUMS = true>
-__global__ void __launch_bounds__(Launch<PL>::WG) __attribute__((amdgpu_waves_per_eu(TM_MINW)))
+__global__ void __launch_bounds__(Launch<PL>::WG) __attribute__((amdgpu_waves_per_eu(PL::WIDE ? PL::WAVES : 1, PL::WAVES)))
 row_kernel(RowArgs a) {
   __shared__ cx<float> lds_all[Launch<PL>::LDS_ELEMS];
   __shared__ float red[Launch<PL>::RED_FLOATS];
@@ -827,7 +1070,7 @@ row_kernel(RowArgs a) {
 // The same kernel with an explicit workgroup size WGT (WGT / T rows per
 // workgroup): the autotuner's wider configurations.
 template <class PL, int MODE, typename IT, bool SUMS, int WGT>
-__global__ void __launch_bounds__(WGT) __attribute__((amdgpu_waves_per_eu(TM_MINW)))
+__global__ void __launch_bounds__(WGT) __attribute__((amdgpu_waves_per_eu(1)))
 row_kernel_w(RowArgs a) {
   __shared__ cx<float> lds_all[Launch<PL, WGT>::LDS_ELEMS];
   __shared__ float red[Launch<PL, WGT>::RED_FLOATS];
@@ -851,21 +1094,12 @@ res64_kernel(RowArgs a) {
   const int row = blockIdx.x * RPW + rloc;
   const bool valid = row < a.P;
   const size_t prow = valid ? (size_t)row : 0;
-  Xbuf<T> xb{lds_all + rloc * PL::LDS_ROW, 0, 0};
-  Tw<T> tw{a.tw64 + (PL::N1 - 1), a.tw64 + (PL::N2 - 1)};
-
-  using L0 = Layout0<PL>;
-  using LL = LayoutL<PL>;
-  int b0[L0::NB];
-#pragma unroll
-  for (int j = 0; j < L0::NB; ++j) b0[j] = L0::base(ltid, j);
-  int kb[LL::NB];
-#pragma unroll
-  for (int j = 0; j < LL::NB; ++j) kb[j] = LL::kbase(ltid, j);
+  const LineFft<PL, T> fft(lds_all + rloc * PL::LDS_ROW, nullptr, ltid, a.tw64 + (PL::N1 - 1), a.tw64 + (PL::N2 - 1));
+  const Where<PL> at(ltid);
   C t[E], x[E];
 #pragma unroll
   for (int i = 0; i < E; ++i) {
-    cx<float> v = a.tin[prow * N + E0(i)];
+    const cx<float> v = a.tin[prow * N + at.elem_l(i) + at.elem_r(i)];
     t[i] = C{(double)v.x, (double)v.y};
   }
   double sr = 0.0, si = 0.0;
@@ -874,13 +1108,14 @@ res64_kernel(RowArgs a) {
     const size_t mbase = (prow * a.K + m) * (size_t)N;
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-      cx<float> w = mk[E0(i)];
+      cx<float> w = mk[at.elem_l(i) + at.elem_r(i)];
       x[i] = cmul(t[i], C{(double)w.x, (double)w.y});
     }
-    fft_forward<PL, T>(x, xb, ltid, tw);
+    __syncthreads();
+    fft.forward(x);
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-      int k = KL(i);
+      const int k = at.freq_l(i) + at.freq_r(i);
       double iv = (double)load_I<IT>(a.I, mbase + k);
       double r = iv - norm2(x[i]);
       sr += r * r;
@@ -895,7 +1130,9 @@ res64_kernel(RowArgs a) {
   }
 }
 
-#undef E0
-#undef KL
+#undef LD_ROW
+#undef ST_ROW
+#undef LD_MASK
+#undef LD_I
 #undef TROW
 }  // namespace tmk

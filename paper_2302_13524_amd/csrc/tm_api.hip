@@ -1292,11 +1292,7 @@ extern "C" int tm_batch_create(tm_ctx* c, int32_t n, const tm_problem* probs, co
     if (gid < 0) { delete b; return fail(c, TM_EUNSUPPORTED, "problem %d: grid %dx%d is not compiled for batches", i, p.d.n1, p.d.n2); }
     if (p.d.P > 0 && (!p.masks || !p.I || !p.t)) { delete b; return fail(c, TM_EINVAL, "problem %d: null pointer", i); }
     b->fns.push_back(fn);
-    auto v = c->variant.find((ilog2(p.d.n1) << 8) | ilog2(p.d.n2));
-    // the batch bodies take the digit order only (eight values per thread in its 512-thread
-    // workgroups measured slower: 45.1 against 42.6 ms for 12 problems)
-    int var = (v == c->variant.end()) ? 0 : (v->second & 1);
-    hp[i].code = 2 * gid + var;
+    hp[i].code = gid;
     int rpi = tmk::batch_rows_per_item(gid);
     for (int blk = 0; blk * rpi < p.d.P; ++blk) items.push_back({i, blk});
     size_t N = (size_t)p.d.n1 * p.d.n2;
@@ -1352,10 +1348,10 @@ extern "C" int tm_batch_create(tm_ctx* c, int32_t n, const tm_problem* probs, co
   b->args.items = ditems;
   b->args.n_items = (int)items.size();
   b->args.tw32 = c->tw32;
-  // persistent grid: every CU holds one 512-thread workgroup (LDS and registers)
+  // persistent grid: every CU holds two 512-thread workgroups (LDS and registers)
   int cus = 0;
   hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
-  b->grid = std::max(1, std::min((int)items.size(), cus > 0 ? cus : 256));
+  b->grid = std::max(1, std::min((int)items.size(), 2 * (cus > 0 ? cus : 256)));
   if (use_graph) {
     hipError_t he = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
     if (he == hipSuccess) he = hipStreamBeginCapture(b->cap, hipStreamCaptureModeRelaxed);
