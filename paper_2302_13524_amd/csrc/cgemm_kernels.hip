@@ -4,7 +4,8 @@
 // (n contiguous). Used by the foci (patterns times the true TM, Sec. 3) and
 // the dense-probing comparator (a random-phase Q in place of the FFTs).
 //
-// Real embedding of the complex product: for one complex k the MFMA's two
+// Short sums run on the FP32 matrix cores, others split into BF16 parts (further
+// down). Real embedding of the complex product: for one complex k the MFMA's two
 // real k are (real part, imaginary part), so that
 //   C_r += [a_r a_i] . [b_r, -b_i],   C_i += [a_r a_i] . [b_i, b_r]:
 // one 32x32x2 MFMA each, lanes 0-31 carrying the real parts of A (and of the
@@ -20,10 +21,16 @@ namespace tmk {
 
 namespace {
 
+// Complex k from which the split product is taken. It costs a second, nearly empty
+// launch (k_cgemm_redo): 2-3 us. FP32 against split, us: 1024 x 1024 x 16 10.2 / 12.5,
+// 1024 x 1024 x 64 23.2 / 18.6, 2048 x 2048 x 48 23.5 / 25.1, 4096 x 4096 x 64 91 / 86,
+// 2286 x 2286 x 8192 4456 / 2335.
+constexpr int SPLIT_K = 64;
+
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
-constexpr int TM = 128, TN = 128, TK = 16;  // tile rows, columns, complex k per step
-constexpr int VPT = TK * TM / 256;           // complex values of a tile per thread and operand
+constexpr int TM = 128, TK = 16;    // tile rows, complex k per step
+constexpr int VPT = TK * TM / 256;  // complex values of a 128-row tile per thread
 
 struct CgemmArgs {
   int M, N, K;
@@ -38,19 +45,21 @@ struct CgemmArgs {
   int veca, vecb;  // 16-byte loads of two complex values allowed
 };
 
-// A tile's 128 x TK complex values in registers, VPT per thread. k-contiguous
-// source (A, or B with trans_b): row r0 + t / 2, k k0 + VPT (t % 2) .. + VPT - 1;
-// n-contiguous source (B): k k0 + t / (TM / VPT), n r0 + VPT (t % (TM / VPT)) ...
+// The (16 VPT) x TK complex values of an operand's tile in registers, VPT per thread.
+// k-contiguous source (A, or B with trans_b): row r0 + t VPT / TK, VPT consecutive k;
+// n-contiguous source (B): k k0 + t / 16, VPT consecutive n.
+template <int V>
 struct Stage {
-  float2 v[VPT];
+  float2 v[V];
 };
 
-__device__ __forceinline__ void fetch(Stage& s, const float2* __restrict__ p, int64_t ld, bool kcontig, bool vec,
-                                      int r0, int k0, int R, int K) {
+template <int VPT, bool kcontig>
+__device__ __forceinline__ void fetch(Stage<VPT>& s, const float2* __restrict__ p, int64_t ld, bool vec, int r0,
+                                      int k0, int R, int K) {
   const int t = threadIdx.x;
-  constexpr int NT = TM / VPT;  // threads along a k-major tile row
-  const int a = kcontig ? r0 + (t >> 1) : k0 + t / NT;                  // fixed index (row, or k)
-  const int b = kcontig ? k0 + VPT * (t & 1) : r0 + VPT * (t % NT);     // first of VPT consecutive
+  constexpr int NK = TK / VPT, NT = 16;  // threads along a row (k contiguous), along a k (n contiguous)
+  const int a = kcontig ? r0 + t / NK : k0 + t / NT;                       // fixed index (row, or k)
+  const int b = kcontig ? k0 + VPT * (t % NK) : r0 + VPT * (t % NT);       // first of VPT consecutive
   const int alim = kcontig ? R : K, blim = kcontig ? K : R;
   const float2* q = p + (int64_t)a * ld + b;
   if (vec && a < alim && b + VPT <= blim) {
@@ -66,63 +75,87 @@ __device__ __forceinline__ void fetch(Stage& s, const float2* __restrict__ p, in
   }
 }
 
-// into LDS as [k][row] (row stride TM complex values)
-__device__ __forceinline__ void stage_store(float2* lds, const Stage& s, bool kcontig) {
+// into LDS as [k][row] (row stride 16 VPT complex values)
+template <int VPT, bool kcontig>
+__device__ __forceinline__ void stage_store(float2* lds, const Stage<VPT>& s) {
   const int t = threadIdx.x;
+  constexpr int R = 16 * VPT, NK = TK / VPT;
   if (kcontig) {
-    const int r = t >> 1, kb = VPT * (t & 1);
+    const int r = t / NK, kb = VPT * (t % NK);
 #pragma unroll
-    for (int i = 0; i < VPT; ++i) lds[(kb + i) * TM + r] = s.v[i];
+    for (int i = 0; i < VPT; ++i) lds[(kb + i) * R + r] = s.v[i];
   } else {
-    constexpr int NT = TM / VPT;
-    const int k = t / NT, nb = VPT * (t % NT);
-    float4* d = (float4*)&lds[k * TM + nb];
+    const int k = t / 16, nb = VPT * (t % 16);
+    float4* d = (float4*)&lds[k * R + nb];
 #pragma unroll
     for (int i = 0; i < VPT / 2; ++i) d[i] = make_float4(s.v[2 * i].x, s.v[2 * i].y, s.v[2 * i + 1].x, s.v[2 * i + 1].y);
   }
 }
 
-__global__ void __launch_bounds__(256, 2) k_cgemm_mfma(CgemmArgs g) {
-  __shared__ float2 sA[2][TK * TM];
-  __shared__ float2 sB[2][TK * TN];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-  const bool hi = lane >= 32;
-  f32x16 cr[2][2], ci[2][2];
+// C tile out: lane holds column n = lane % 32 of each 32 x 32 block, rows
+// 8 q + 4 (lane / 32) + r for element 4 q + r
+template <int NJ>
+__device__ __forceinline__ void store_tile(const CgemmArgs& g, const f32x16 (&cr)[2][NJ], const f32x16 (&ci)[2][NJ], int m0,
+                                           int n0) {
+  const int lane = threadIdx.x & 63;
+  const float sgn = g.conj_c ? -1.f : 1.f;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int m = m0 + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+        const int n = n0 + 32 * j + (lane & 31);
+        const float x = cr[i][j][e], y = ci[i][j][e];
+        if (m < g.M && n < g.N) g.C[(int64_t)m * g.ldc + n] = make_float2(x, sgn * y);
+      }
+}
+
+// One 128 x (64 NJ) tile on the FP32 matrix cores; four waves of 64 x (32 NJ).
+// LDS: two buffers of TK (128 + 64 NJ) complex values.
+template <int NJ, bool BK>
+__device__ __forceinline__ void tile_f32(const CgemmArgs& g, int m0, int n0, float2* lds) {
+  constexpr int TN = 64 * NJ;
+  float2* const sA[2] = {lds, lds + TK * (TM + TN)};
+  float2* const sB[2] = {lds + TK * TM, lds + TK * (TM + TN) + TK * TM};
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 32 * NJ;
+  const bool hi = lane >= 32;
+  f32x16 cr[2][NJ], ci[2][NJ];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) cr[i][j][e] = ci[i][j][e] = 0.f;
 
-  const bool bk = g.trans_b != 0;
-  Stage ra, rb;
-  fetch(ra, g.A, g.lda, true, g.veca != 0, m0, 0, g.M, g.K);
-  fetch(rb, g.B, g.ldb, bk, g.vecb != 0, n0, 0, g.N, g.K);
+  Stage<VPT> ra;
+  Stage<4 * NJ> rb;
+  fetch<VPT, true>(ra, g.A, g.lda, g.veca != 0, m0, 0, g.M, g.K);
+  fetch<4 * NJ, BK>(rb, g.B, g.ldb, g.vecb != 0, n0, 0, g.N, g.K);
   const int nk = (g.K + TK - 1) / TK;
   for (int ks = 0; ks < nk; ++ks) {
     float2* a_s = sA[ks & 1];
     float2* b_s = sB[ks & 1];
     // this buffer's last readers (step ks - 2) passed the barrier of step ks - 1
-    stage_store(a_s, ra, true);
-    stage_store(b_s, rb, bk);
+    stage_store<VPT, true>(a_s, ra);
+    stage_store<4 * NJ, BK>(b_s, rb);
     __syncthreads();
     if (ks + 1 < nk) {
-      fetch(ra, g.A, g.lda, true, g.veca != 0, m0, (ks + 1) * TK, g.M, g.K);
-      fetch(rb, g.B, g.ldb, bk, g.vecb != 0, n0, (ks + 1) * TK, g.N, g.K);
+      fetch<VPT, true>(ra, g.A, g.lda, g.veca != 0, m0, (ks + 1) * TK, g.M, g.K);
+      fetch<4 * NJ, BK>(rb, g.B, g.ldb, g.vecb != 0, n0, (ks + 1) * TK, g.N, g.K);
     }
 #pragma unroll
     for (int kk = 0; kk < TK; ++kk) {
-      float av[2], br[2], bi[2];
+      float av[2], br[NJ], bi[NJ];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const float2 a = a_s[kk * TM + wm + 32 * i + (lane & 31)];
         av[i] = hi ? a.y : a.x;
       }
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         const float2 b = b_s[kk * TN + wn + 32 * j + (lane & 31)];
         br[j] = hi ? -b.y : b.x;
         bi[j] = hi ? b.x : b.y;
@@ -130,25 +163,272 @@ __global__ void __launch_bounds__(256, 2) k_cgemm_mfma(CgemmArgs g) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NJ; ++j) {
           cr[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], br[j], cr[i][j], 0, 0, 0);
           ci[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bi[j], ci[i][j], 0, 0, 0);
         }
     }
   }
-  // lane holds column n = lane % 32 of each 32 x 32 block, rows 8 q + 4 (lane / 32) + r for element 4 q + r
-  const float sgn = g.conj_c ? -1.f : 1.f;
+  store_tile<NJ>(g, cr, ci, m0 + wm, n0 + wn);
+}
+
+template <bool BK>
+__global__ void __launch_bounds__(256, 2) k_cgemm_mfma(CgemmArgs g) {
+  __shared__ float2 lds[2 * TK * (TM + 128)];
+  tile_f32<2, BK>(g, blockIdx.y * TM, blockIdx.x * 128, lds);
+}
+
+// ---------------------------------------------------------------- split products
+// The same product on the BF16 matrix cores (16 times the FP32 rate). Every FP32
+// value is the exact sum of three BF16 values, each the nearest to what the ones
+// before it leave,
+//   x = x1 + x2 + x3,  |x2| <= 2^-8 |x|,  |x3| <= 2^-16 |x|,
+// and a b = a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a3 b1 + a2 b2): six products that the
+// FP32 sums take in exactly; what is left out is below 2^-23 of the product and of
+// either sign. The BF16 cores cut off what falls below the accumulator's last place,
+// so that a long chain of one sign comes out short (by 1.6e-6 over 8192 k): the six
+// products of 8 complex k are summed by themselves, the smallest first, and added to
+// the total by a rounding FP32 add. Error against 64 bits, largest over sum |a||b|:
+// 2286 x 2286 x 8192 normal values 6.4e-8 (FP32 cores 2.5e-7), conj(A) A^T of unit
+// phases, whose diagonal is one sign, 5.4e-8 (2.3e-7).
+//
+// Real embedding as above over k = (re, im) pairs; the operand for C_r flips
+// the imaginary parts' signs, the one for C_i swaps each pair.
+//
+// Values outside [2^-48, 2^48] (0 apart) could take a small product below the
+// normal range, and infinities and NaN do not split; the tile sees either while
+// it stages them, stops, and is left to k_cgemm_redo.
+//
+// 128 x 64 tiles and three workgroups per CU (168 VGPRs, 48 KB of LDS): 2286 x 2286
+// has 648 of them for 768 places, where 128 x 128 tiles at two per CU would leave a
+// third of the chip idle. The operands are split while they are staged, so nothing
+// is read twice and no workspace is kept; B is stored once for C_r and once for C_i.
+// 2335 us at 2286 x 2286 x 8192 (FP32 cores 4456): 880 TFLOP/s of BF16 products, with
+// the splitting (VALU) about as long as the products and beside them.
+constexpr int SN = 64;                                        // tile columns
+constexpr int S_PLANE_A = TM * TK, S_PLANE_B = SN * TK;  // words (two BF16) of a plane
+
+typedef __attribute__((__vector_size__(8 * sizeof(short)))) short bf16x8_t;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+// 16-byte chunk c (8 k) of a row in LDS: rows of 64 bytes, chunks permuted so that the
+// lanes of a fragment read (consecutive rows) cover all banks
+__device__ __forceinline__ int chunk_at(int row, int c) { return row * 4 + (c ^ ((row >> 1) & 3)); }
+
+// the three planes of two values, packed (low half: a)
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+  const bf16x2_t r = __builtin_convertvector(f32x2{a, b}, bf16x2_t);  // to nearest
+  unsigned w;
+  __builtin_memcpy(&w, &r, sizeof w);
+  return w;
+}
+
+__device__ __forceinline__ void split2(float a, float b, unsigned& p1, unsigned& p2, unsigned& p3) {
+  p1 = pack_bf16(a, b);
+  const float a2 = a - __uint_as_float(p1 << 16), b2 = b - __uint_as_float(p1 & 0xffff0000u);
+  p2 = pack_bf16(a2, b2);
+  const float a3 = a2 - __uint_as_float(p2 << 16), b3 = b2 - __uint_as_float(p2 & 0xffff0000u);
+  p3 = pack_bf16(a3, b3);
+}
+
+// range of the nonzero magnitudes seen, as bit patterns (zero counts as largest for lo)
+struct Seen {
+  unsigned lo = 0xffffffffu;
+  int hi = 0;
+  __device__ __forceinline__ void add(float a, float b) {
+    const unsigned ua = __float_as_uint(a) & 0x7fffffffu, ub = __float_as_uint(b) & 0x7fffffffu;
+    hi = max(hi, max((int)ua, (int)ub));
+    lo = min(lo, min(ua - 1u, ub - 1u));
+  }
+  __device__ __forceinline__ bool splits() const {
+    return (hi == 0 || lo >= (79u << 23) - 1u) && hi <= (int)(175u << 23);  // 2^-48, 2^48
+  }
+};
+
+// One unit: four complex k of one row (a 16-byte chunk of each plane). A thread
+// stages two units of A and one of B per step. Rows past the end repeat the last
+// row (their results are not stored), k past the end are zeroed in the last step;
+// the buffer's range keeps every load inside the operand.
+struct Unit {
+  float2 v[4];
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float2* p, int64_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)(bytes < 0x7fffffff ? bytes : 0x7fffffff), 0x00020000);
+}
+
+// 32 bytes at byte offset `at`, or four values ld bytes apart
+template <bool wide>
+__device__ __forceinline__ void unit_load(Unit& u, __amdgpu_buffer_rsrc_t r, int at, int ld) {
+  if (wide) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(r, at + 16 * i, 0, 0);
+      u.v[2 * i] = make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
+      u.v[2 * i + 1] = make_float2(__uint_as_float(w[2]), __uint_as_float(w[3]));
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, at + i * ld, 0, 0);
+      u.v[i] = make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
+    }
+  }
+}
+
+// the unit's first `left` values are inside K
+__device__ __forceinline__ void unit_tail(Unit& u, int left) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (i >= left) u.v[i] = make_float2(0.f, 0.f);
+}
+
+// A unit into its three LDS planes (chunk index of the unit, words of a plane); B's
+// for C_r and, three planes on, for C_i
+template <bool isB>
+__device__ __forceinline__ void split_store(unsigned* lds, int plane, int chunk, const Unit& u, Seen& seen) {
+  u32x4 w[3];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    unsigned x, y, z;
+    seen.add(u.v[i].x, u.v[i].y);
+    split2(u.v[i].x, u.v[i].y, x, y, z);
+    w[0][i] = x, w[1][i] = y, w[2][i] = z;
+  }
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    unsigned* const at = lds + p * plane + 4 * chunk;
+    if (!isB) {
+      *(u32x4*)at = w[p];
+    } else {
+      u32x4 r, q;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        r[e] = w[p][e] ^ 0x80000000u;                           // (re, -im)
+        q[e] = __builtin_amdgcn_alignbit(w[p][e], w[p][e], 16);  // (im, re)
+      }
+      *(u32x4*)at = r;
+      *(u32x4*)(at + 3 * plane) = q;
+    }
+  }
+}
+
+__device__ __forceinline__ bf16x8_t as_bf16(u32x4 v) {
+  bf16x8_t r;
+  __builtin_memcpy(&r, &v, sizeof r);
+  return r;
+}
+
+// what a stopped tile leaves in its first element: a NaN that no sum gives (one in
+// the inputs only costs the tile a second, equal computation)
+constexpr unsigned REDO = 0x7fc5a5a5u;
+
+template <bool BK>
+__global__ void __launch_bounds__(256, 3) k_cgemm_split(CgemmArgs g) {
+  __shared__ __attribute__((aligned(16))) unsigned lds[3 * (S_PLANE_A + 2 * S_PLANE_B)];
+  __shared__ int bad;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 32;
+  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * SN;
+  unsigned* const sA = lds;
+  unsigned* const sB = lds + 3 * S_PLANE_A;
+  if (tid == 0) bad = 0;
+  f32x16 cr[2][1], ci[2][1];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int e = 0; e < 16; ++e) cr[i][0][e] = ci[i][0][e] = 0.f;
+
+  // staging: A rows tid / 4 and + 64, k unit tid % 4; B the same or, n-contiguous,
+  // column tid % 64 and k unit tid / 64
+  const int rows = min(TM, g.M - m0) - 1, cols = min(SN, g.N - n0) - 1;
+  const int kuA = tid & 3, kuB = BK ? tid & 3 : wave;
+  const int rB = BK ? tid >> 2 : lane;
+  const int atA0 = (min(tid >> 2, rows) * (int)g.lda + 4 * kuA) * 8;
+  const int atA1 = (min((tid >> 2) + 64, rows) * (int)g.lda + 4 * kuA) * 8;
+  const int ldB = (int)g.ldb * 8;
+  const int atB = BK ? min(rB, cols) * ldB + 32 * kuB : 4 * kuB * ldB + min(rB, cols) * 8;
+  const float2* const pA = g.A + (int64_t)m0 * g.lda;
+  const float2* const pB = g.B + (BK ? (int64_t)n0 * g.ldb : n0);
+  Unit ra0, ra1, rb;
+  Seen seen;
+  auto load = [&](int k0) {
+    const auto A = buffer_of(pA + k0, ((int64_t)rows * g.lda + g.K - k0) * 8);
+    const auto B = BK ? buffer_of(pB + k0, ((int64_t)cols * g.ldb + g.K - k0) * 8)
+                      : buffer_of(pB + (int64_t)k0 * g.ldb, ((int64_t)(g.K - k0 - 1) * g.ldb + cols + 1) * 8);
+    if (k0 + TK <= g.K) {
+      unit_load<true>(ra0, A, atA0, 0);
+      unit_load<true>(ra1, A, atA1, 0);
+      unit_load<BK>(rb, B, atB, ldB);
+    } else {  // no load straddles the end of the range
+      unit_load<false>(ra0, A, atA0, 8);
+      unit_load<false>(ra1, A, atA1, 8);
+      unit_load<false>(rb, B, atB, BK ? 8 : ldB);
+    }
+  };
+  load(0);
+  for (int k0 = 0; k0 < g.K; k0 += TK) {
+    __syncthreads();  // the last step's reads are done
+    if (k0 + TK > g.K) {
+      unit_tail(ra0, g.K - k0 - 4 * kuA);
+      unit_tail(ra1, g.K - k0 - 4 * kuA);
+      unit_tail(rb, g.K - k0 - 4 * kuB);
+    }
+    split_store<false>(sA, S_PLANE_A, chunk_at(tid >> 2, kuA), ra0, seen);
+    split_store<false>(sA, S_PLANE_A, chunk_at((tid >> 2) + 64, kuA), ra1, seen);
+    split_store<true>(sB, S_PLANE_B, chunk_at(rB, kuB), rb, seen);
+    if (!seen.splits()) bad = 1;
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(bad)) {  // next written behind the next barrier
+      if (tid == 0) g.C[(int64_t)m0 * g.ldc + n0].x = __uint_as_float(REDO);
+      return;
+    }
+    if (k0 + TK < g.K) load(k0 + TK);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = m0 + wm + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        const int n = n0 + wn + 32 * j + (lane & 31);
-        const float x = cr[i][j][e], y = ci[i][j][e];
-        if (m < g.M && n < g.N) g.C[(int64_t)m * g.ldc + n] = make_float2(x, sgn * y);
+    for (int k16 = 0; k16 < 2; ++k16) {
+      const int c = 2 * k16 + (lane >> 5);
+      bf16x8_t b[2][3];
+#pragma unroll
+      for (int part = 0; part < 2; ++part)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          b[part][p] = as_bf16(*(const u32x4*)(sB + (3 * part + p) * S_PLANE_B + 4 * chunk_at(wn + (lane & 31), c)));
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        bf16x8_t a[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          a[p] = as_bf16(*(const u32x4*)(sA + p * S_PLANE_A + 4 * chunk_at(wm + 32 * i + (lane & 31), c)));
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+          f32x16 t = {};
+#pragma unroll
+          for (int lev = 2; lev >= 0; --lev)
+#pragma unroll
+            for (int p = lev; p >= 0; --p)
+              t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[lev - p], b[part][p], t, 0, 0, 0);
+          f32x16& to = part ? ci[i][0] : cr[i][0];
+#pragma unroll
+          for (int e = 0; e < 16; ++e) to[e] += t[e];
+        }
       }
+    }
+  }
+  store_tile<1>(g, cr, ci, m0 + wm, n0 + wn);
+}
+
+// the tiles that the split could not take
+template <bool BK>
+__global__ void __launch_bounds__(256, 2) k_cgemm_redo(CgemmArgs g) {
+  __shared__ float2 lds[2 * TK * (TM + SN)];
+  __shared__ bool redo;
+  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * SN;
+  if (threadIdx.x == 0) redo = __float_as_uint(g.C[(int64_t)m0 * g.ldc + n0].x) == REDO;
+  __syncthreads();
+  if (redo) tile_f32<1, BK>(g, m0, n0, lds);
 }
 
 }  // namespace
@@ -173,8 +453,15 @@ int launch_cgemm(int M, int N, int K, const void* A, int64_t lda, const void* B,
   g.conj_c = conj_c;
   g.veca = lda % 2 == 0 && (uintptr_t)A % 16 == 0;
   g.vecb = ldb % 2 == 0 && (uintptr_t)B % 16 == 0;
-  dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM);
-  k_cgemm_mfma<<<grid, 256, 0, (hipStream_t)stream>>>(g);
+  // 32-bit offsets inside a tile's rows
+  if (K >= SPLIT_K && lda < (1 << 20) && ldb < (1 << 20)) {
+    const dim3 grid((N + SN - 1) / SN, (M + TM - 1) / TM);
+    (trans_b ? k_cgemm_split<true> : k_cgemm_split<false>)<<<grid, 256, 0, (hipStream_t)stream>>>(g);
+    (trans_b ? k_cgemm_redo<true> : k_cgemm_redo<false>)<<<grid, 256, 0, (hipStream_t)stream>>>(g);
+  } else {
+    const dim3 grid((N + 127) / 128, (M + TM - 1) / TM);
+    (trans_b ? k_cgemm_mfma<true> : k_cgemm_mfma<false>)<<<grid, 256, 0, (hipStream_t)stream>>>(g);
+  }
   return (int)hipGetLastError();
 }
 
