@@ -148,7 +148,7 @@ void* ws_get(tm_ctx* c, int id, size_t bytes) {
 enum WsId {
   WS_SUMS = 1, WS_SUMS64, WS_ROWSUM, WS_ROWMEAN, WS_VPREV,
   WS_LB_G, WS_LB_GP, WS_LB_D, WS_LB_S, WS_LB_Y, WS_LB_SC, WS_LB_ST, WS_TPREV, WS_VSCALE, WS_LZ_V, WS_LZ_H, WS_LZ_Y, WS_PRE_PART,
-  WS_PRE_COUNT, WS_FOCI_U, WS_FOCI_E, WS_DENSE_Y, WS_PROP_X, WS_PROP_H, WS_PROP_ONES, WS_WTAB,
+  WS_PRE_MASK, WS_FOCI_U, WS_FOCI_E, WS_DENSE_Y, WS_PROP_X, WS_PROP_H, WS_PROP_ONES, WS_WTAB,
   WS_PH_BASE = 100
 };
 
@@ -1566,9 +1566,10 @@ extern "C" int tm_pre_fiber_mask(tm_ctx* c, const double* energy, int32_t npix, 
   if (npix < 1 || npix > tmk::PRE_MASK_MAX) return fail(c, TM_EINVAL, "npix=%d outside 1..%d", npix, tmk::PRE_MASK_MAX);
   if (!(frac > 0.0 && frac <= 1.0)) return fail(c, TM_EINVAL, "frac must be in (0, 1]");
   HIPCHK(c, hipSetDevice(c->device));
-  int32_t* cnt = (int32_t*)ws_get(c, WS_PRE_COUNT, sizeof(int32_t));
-  if (!cnt) return fail(c, TM_ENOMEM, "workspace");
-  int e = tmk::launch_pre_mask(energy, npix, frac, pix, cnt, stream);
+  void* scratch = ws_get(c, WS_PRE_MASK, tmk::pre_mask_scratch(npix));
+  if (!scratch) return fail(c, TM_ENOMEM, "workspace");
+  int32_t* cnt = nullptr;
+  int e = tmk::launch_pre_mask(energy, npix, frac, pix, scratch, &cnt, stream);
   if (e) return hipfail(c, e, "fiber mask");
   int32_t h = 0;
   HIPCHK(c, hipMemcpyAsync(&h, cnt, sizeof(int32_t), hipMemcpyDeviceToHost, (hipStream_t)stream));
