@@ -33,8 +33,9 @@ using Default = std::conditional_t<kWide, WidePlan<kWide ? GL1 : 6, kWide ? GL2 
 template <class PLg, typename IT>
 static int launch_t(int mode, const RowArgs& a, hipStream_t s) {
   using LC = Launch<PLg>;
-  dim3 grid((a.P + LC::RPW - 1) / LC::RPW), block(LC::WG);
   if (a.P <= 0) return 0;
+  if (split_mode(mode) && (a.split < 1 || a.split > a.K)) return (int)hipErrorInvalidValue;
+  dim3 grid((a.P + LC::RPW - 1) / LC::RPW * (split_mode(mode) ? a.split : 1)), block(LC::WG);
   switch (mode) {
     case M_FWD_FIELD: row_kernel<PLg, M_FWD_FIELD, IT><<<grid, block, 0, s>>>(a); break;
     case M_FWD_INT: row_kernel<PLg, M_FWD_INT, IT><<<grid, block, 0, s>>>(a); break;
@@ -204,8 +205,8 @@ void TM_CAT(row_cfgshape, GL1, GL2)(int cfg, int* wg, int* rpw, int* ept) {
 }
 
 void TM_CAT(row_shape, GL1, GL2)(int* wg, int* rpw) {
-  *wg = Launch<Plan<GL1, GL2>>::WG;
-  *rpw = Launch<Plan<GL1, GL2>>::RPW;
+  *wg = Launch<Default<0>>::WG;
+  *rpw = Launch<Default<0>>::RPW;
 }
 
 }  // namespace tmk

@@ -25,9 +25,14 @@ enum Mode : int {
   M_LANCZOS = 13,    // Lanczos step on A^H diag(w) A: v_next = (M v - alpha v - beta v_prev)/||.|| -> tout, lz_out
   // learned weighting of the spectral start: w = T(I / mean(I_p)) from the table wtab
   M_LANCZOS_T = 14,  // M_LANCZOS with the weights read from I (the learned weights, FP32 [P][K][N])
-  M_WAPPLY = 15,     // y = A^H diag(w) A t with the learned weights      -> tout, sums {||y||^2}
-  M_WBACK = 16       // gw = Re(conj(A d) (A t)) -> yout float [P][K][N]; x = A^H diag(w) A d -> tout
+  M_WAPPLY = 15,     // parts of y = A^H diag(w) A t with the learned weights -> tout [split][P][N]
+  M_WBACK = 16       // gw = Re(conj(A d) (A t)) -> yout float [P][K][N] (or added to it); parts of
+                     // A^H diag(w) A d -> tout
 };
+
+// Modes whose masks may be shared out over `split` workgroups per row: those that write
+// each mask's values, and those whose caller adds up the parts.
+constexpr bool split_mode(int m) { return m == M_FWD_FIELD || m == M_FWD_INT || m == M_WAPPLY || m == M_WBACK; }
 
 // Modes that weight by the learned table (the row kernels look it up per measurement).
 constexpr bool learned_mode(int m) { return m == M_WAPPLY || m == M_WBACK; }
@@ -64,6 +69,8 @@ struct RowArgs {
   float wtab_scale;        // (nt - 1) / xmax
   float wtab_last;         // nt - 1
   int out_bf16;            // M_FWD_INT output type
+  int add_out;             // M_WBACK: gw is added to yout
+  int split;               // split_mode: workgroups per row (1 .. K), part i the masks [i K / split, (i + 1) K / split)
   const cx<float>* tw32;   // twiddle tables, table of length L at offset L-1
   const cx<double>* tw64;
   // M_ERC with lz_k > 0: the row is the Ritz vector sum_j y_j v_j of a Lanczos
@@ -388,7 +395,7 @@ __device__ __forceinline__ float wtab_eval(const RowArgs& a, float x) {
 // (batch sweep over 12 problems 2.60 -> 1.65 ms), while in the inlined kernel
 // the same order costs 5 % (its own schedule overlaps them already).
 template <class PL, int MODE, typename IT, bool SUMS, int WGT, bool OOL = false>
-__device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>* lds_all, float* red) {
+__device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>* lds_all, float* red) {
   // Every buffer is in device global memory: the accesses below go through
   // global-address-space pointers, so that where this body is not inlined into
   // a kernel they stay global (not flat) loads and stores, which do not share
@@ -402,6 +409,9 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
   const int tid = threadIdx.x;
   const int rloc = tid / PL::T;
   const int ltid = tid % PL::T;
+  constexpr bool SPL = split_mode(MODE);
+  const int blk = SPL ? wgi / a.split : wgi, part = SPL ? wgi - blk * a.split : 0;
+  const int m0 = SPL ? part * a.K / a.split : 0, m1 = SPL ? (part + 1) * a.K / a.split : a.K;
   const int row = blk * RPW + rloc;
   const bool valid = row < a.P;
   const size_t prow = valid ? (size_t)row : 0;
@@ -623,9 +633,9 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
   C mnext[PF ? E : 1];  // the next mask's values, loaded during the last inverse pass
   if constexpr (PF) {
 #pragma unroll
-    for (int i = 0; i < E; ++i) mnext[i] = ld<W>(a.masks, at.elem_l(i), at.elem_r(i));
+    for (int i = 0; i < E; ++i) mnext[i] = ld<W>(a.masks + (size_t)m0 * N, at.elem_l(i), at.elem_r(i));
   }
-  for (int m = 0; m < a.K; ++m) {
+  for (int m = m0; m < m1; ++m) {
     if constexpr (!KEEP_T) again = hidden_zero();
     const C* mk = a.masks + (size_t)m * N;
     const size_t mbase = (brow * a.K + m) * (size_t)N;
@@ -682,7 +692,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
         for (int i = 0; i < E; ++i) x[i] = cmul(TROW(i), LD_MASK(i));
       }
       if constexpr (MODE == M_FWD_FIELD || MODE == M_FWD_INT || MODE == M_LS || MODE == M_ALS) {
-        if (m > 0) fft.fence();
+        if (m > m0) fft.fence();
       }
       fft.forward(x);
     }
@@ -807,12 +817,26 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
       }
         fft.fence();
         fft.forward(x);
+        // y's registers become gw and the intensities, whose loads go out together (one at
+        // a time, with the lookup between: 57 us for 128 rows at 128 x 64, so 39)
 #pragma unroll
-        for (int i = 0; i < E; ++i) {
-          const float w = wtab_eval(a, LD_I(i) * inv_mean);
-          if (valid) st_f<W>((float*)a.yout + mbase, rk + at.freq_l(i), at.freq_r(i), rdot(y[i], x[i]));
-          x[i] = scl(x[i], w);
+        for (int i = 0; i < E; ++i) y[i].x = rdot(y[i], x[i]);
+        if (a.add_out) {
+#pragma unroll
+          for (int i = 0; i < E; ++i) y[i].y = ld_I<W, float>((const float*)a.yout + mbase, rk + at.freq_l(i), at.freq_r(i));
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < E; ++i) y[i].x += y[i].y;
         }
+#pragma unroll
+        for (int i = 0; i < E; ++i) y[i].y = LD_I(i);
+        __builtin_amdgcn_sched_barrier(0);
+        if (valid) {
+#pragma unroll
+          for (int i = 0; i < E; ++i) st_f<W>((float*)a.yout + mbase, rk + at.freq_l(i), at.freq_r(i), y[i].x);
+        }
+#pragma unroll
+        for (int i = 0; i < E; ++i) x[i] = scl(x[i], wtab_eval(a, y[i].y * inv_mean));
       }
       if constexpr (MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_SPEC || MODE == M_LANCZOS ||
                     MODE == M_AGRAD || MODE == M_LANCZOS_T || MODE == M_WAPPLY) {
@@ -867,7 +891,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
       }
       if constexpr (PF) {
         const C* mk1 = mk + N;
-        const bool more = m + 1 < a.K;
+        const bool more = m + 1 < m1;
         fft.inverse(x, [&]() {
           if (more) {
 #pragma unroll
@@ -1016,17 +1040,10 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int blk, cx<float>
         if (a.sums) gw(a.sums)[prow * NSUM + 0] = lam;
       }
     }
-  } else if constexpr (MODE == M_WAPPLY) {
-    KSum q[1];
-    q[0] = KSum{0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < E; ++i) q[0].add(norm2(g[i]));
-    float o1[1];
-    row_reduce<PL::T, WG, 1>(q, red, tid, o1);
+  } else if constexpr (MODE == M_WAPPLY || MODE == M_WBACK) {
     if (valid) {
 #pragma unroll
-      for (int i = 0; i < E; ++i) ST_ROW(a.tout + brow * N, i, g[i]);
-      if (ltid == 0) gw(a.sums)[prow * NSUM + 0] = o1[0];
+      for (int i = 0; i < E; ++i) ST_ROW(a.tout + ((size_t)part * a.P + brow) * N, i, g[i]);
     }
   } else {
     float scale = 1.f;

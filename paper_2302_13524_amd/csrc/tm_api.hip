@@ -31,6 +31,7 @@ constexpr int TM_PROF_MODES = 24;  // row-kernel modes 0..16, 20 L-BFGS directio
 
 struct tm_ctx {
   int device = 0;
+  int cus = 256;
   std::string err;
   tmk::cx<float>* tw32 = nullptr;
   tmk::cx<double>* tw64 = nullptr;
@@ -175,11 +176,25 @@ bool ritz_in_sweep(const tm_retrieve_opts& o) {
          (o.start == TM_START_LANCZOS || o.start == TM_START_LEARNED);
 }
 
+// Workgroups per row for the modes that can share out a row's masks: as many as two
+// workgroups per CU leave room for. With as many rows as that one workgroup runs all
+// masks, which reads the row once. 128 x 64, one and split, us: forward of 37 rows, 4
+// masks 23 / 11; the learned weighting's step of 128 rows, 4 masks 41 / 25 and backward
+// 100 / 57.
+int mask_split(const tm_ctx* c, const tm_dims& d) {
+  int wg = 0, rpw = 0;
+  tmk::row_launch_shape(ilog2(d.n1), ilog2(d.n2), &wg, &rpw);
+  if (rpw < 1) return 1;
+  const int wgs = (d.P + rpw - 1) / rpw;
+  return std::max(1, std::min(d.K, 2 * c->cus / std::max(wgs, 1)));
+}
+
 tmk::RowArgs base_args(tm_ctx* c, const tm_dims& d, const tm_c32* masks) {
   tmk::RowArgs a;
   memset(&a, 0, sizeof a);
   a.P = d.P;
   a.K = d.K;
+  a.split = mask_split(c, d);
   a.masks = (const tmk::cx<float>*)masks;
   a.tw32 = c->tw32;
   a.tw64 = c->tw64;
@@ -277,6 +292,7 @@ int tm_create(tm_ctx** out, int device) {
   }
   tm_ctx* c = new tm_ctx;
   c->device = device;
+  hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, device);
   c->scratch = sp;
   // Twiddle tables W_L^i = exp(-2 pi j i / L) for every power of two L <= TW_MAX,
   // the table of length L at offset L - 1; FP64 values, FP32 rounded once.
@@ -1808,22 +1824,23 @@ static int wtab_grad(tm_ctx* c, tmk::row_launcher fn, const tm_dims& d, const tm
   const int N = d.n1 * d.n2, B = d.P;
   const size_t row = (size_t)B * N * sizeof(tm_c32);
   char* U = (char*)ws_get(c, WS_PH_BASE + 32, row * (k + 1));
-  void* Y = ws_get(c, WS_PH_BASE + 33, row);
-  void* G = ws_get(c, WS_PH_BASE + 34, row);
+  const int split = mask_split(c, d);  // parts of A^H diag(w) A u
+  void* Y = ws_get(c, WS_PH_BASE + 33, row * split);
+  void* G = ws_get(c, WS_PH_BASE + 34, row * split);
   void* Gy = ws_get(c, WS_PH_BASE + 35, row);
   float* gw = (float*)ws_get(c, WS_PH_BASE + 36, (size_t)B * d.K * N * sizeof(float));
   float* nrm = (float*)ws_get(c, WS_PH_BASE + 37, (size_t)k * B * sizeof(float));
   float* fid = (float*)ws_get(c, WS_PH_BASE + 38, (size_t)B * sizeof(float));
+  const int hb = tmk::wnet_hist_parts(B, d.K * N, c->cus);
+  float* hist = (float*)ws_get(c, WS_PH_BASE + 49, (size_t)hb * nt * sizeof(float));
   double* rowsum = (double*)ws_get(c, WS_ROWSUM, (size_t)B * sizeof(double));
   float* rowmean = (float*)ws_get(c, WS_ROWMEAN, (size_t)B * sizeof(float));
-  float* sums = (float*)ws_get(c, WS_SUMS, (size_t)B * tmk::NSUM * sizeof(float));
-  if (!U || !Y || !G || !Gy || !gw || !nrm || !fid || !rowsum || !rowmean || !sums)
+  if (!U || !Y || !G || !Gy || !gw || !nrm || !fid || !hist || !rowsum || !rowmean)
     return fail(c, TM_ENOMEM, "training workspace");
   auto Uj = [&](int j) { return (void*)(U + row * j); };
   int e = tmk::launch_row_isum(I, ibf, (int64_t)d.K * N, B, rowsum, rowmean, stream);
   if (!e) e = tmk::launch_copy(Uj(0), v0, (int64_t)row, stream);
   if (!e) e = tmk::launch_row_rescale(Uj(0), N, B, 0, nullptr, 1.0, stream);
-  if (!e) e = tmk::launch_fill_zero(dtab, (int64_t)nt * sizeof(float), stream);
   if (e) return hipfail(c, e, "training setup");
   tmk::RowArgs a = base_args(c, d, masks);
   a.I = I;
@@ -1831,28 +1848,30 @@ static int wtab_grad(tm_ctx* c, tmk::row_launcher fn, const tm_dims& d, const tm
   a.wtab = tab;
   a.wtab_scale = (float)(nt - 1) / xmax;
   a.wtab_last = (float)(nt - 1);
-  a.sums = sums;
   int r;
   for (int j = 0; j < k; ++j) {
     a.tin = (const tmk::cx<float>*)Uj(j);
     a.tout = (tmk::cx<float>*)Y;
     if ((r = run_row(c, fn, tmk::M_WAPPLY, ibf, a, stream))) return r;
-    e = tmk::wnet_normalise(Y, sums, tmk::NSUM, B, N, Uj(j + 1), nrm + (size_t)j * B, stream);
+    e = tmk::wnet_normalise(Y, split, B, N, Uj(j + 1), nrm + (size_t)j * B, stream);
     if (e) return hipfail(c, e, "normalise");
   }
   e = tmk::wnet_loss(Uj(k), t, B, N, G, fid, loss, stream);
   if (e) return hipfail(c, e, "loss");
   for (int j = k - 1; j >= 0; --j) {
-    e = tmk::wnet_normback(G, Uj(j + 1), nrm + (size_t)j * B, B, N, Gy, stream);
+    e = tmk::wnet_normback(G, j == k - 1 ? 1 : split, Uj(j + 1), nrm + (size_t)j * B, B, N, Gy, stream);
     if (e) return hipfail(c, e, "normalisation backward");
     a.tin = (const tmk::cx<float>*)Uj(j);
     a.din = (const tmk::cx<float>*)Gy;
     a.yout = gw;
+    a.add_out = j < k - 1;
     a.tout = (tmk::cx<float>*)G;
     if ((r = run_row(c, fn, tmk::M_WBACK, ibf, a, stream))) return r;
-    e = tmk::wnet_hist(gw, I, ibf, rowmean, B, d.K * N, nt, xmax, dtab, stream);
-    if (e) return hipfail(c, e, "table gradient");
   }
+  // The lookup is the same at every step, so its adjoint is applied once, to the sum
+  // of the steps' gw (20 steps of 128 x 4 x 8192: 45 us once, not per step).
+  e = tmk::wnet_hist(gw, I, ibf, rowmean, B, d.K * N, nt, xmax, hist, hb, dtab, stream);
+  if (e) return hipfail(c, e, "table gradient");
   return TM_OK;
 }
 

@@ -93,15 +93,68 @@ __global__ void __launch_bounds__(WB) k_pairs(const float* __restrict__ O, int n
   tab[2 * b + 1] = (b + 1 < nt) ? O[b + 1] - v : 0.f;
 }
 
-// u = y / ||y|| per row, ||y||^2 given (sums[p * nsum]); n[p] = ||y||
-__global__ void __launch_bounds__(WB) k_normalise(const float2* __restrict__ y, const float* __restrict__ sums,
-                                                   int nsum, int N, float2* u, float* n) {
+// The row steps between the applications of A^H diag(w) A: one workgroup per row, the
+// row in registers. Bound by the latency of one row's loads and one reduction: 10.8 and
+// 11.5 us for 128 rows of 8192 in four parts (10.6 and 16.4 with 256 threads a row,
+// read twice, without parts).
+constexpr int RB = 1024, RV = 8;  // N <= RB RV
+
+// the total of v over the workgroup, in every thread
+__device__ __forceinline__ double row_sum(double v) {
+  __shared__ double red[RB / 64];
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = 0.0;
+  for (int w = 0; w < RB / 64; ++w) s += red[w];
+  return s;
+}
+
+// value of row p at this thread's k-th place, the parts added in order
+__device__ __forceinline__ void sum_parts(float2 (&y)[RV], const float2* __restrict__ parts, int np, int P, int N) {
+  const size_t row = (size_t)blockIdx.x * N;
+#pragma unroll
+  for (int k = 0; k < RV; ++k) y[k] = make_float2(0.f, 0.f);
+  // two parts' loads in flight
+  for (int j = 0; j < np; j += 2) {
+    const float2* q0 = parts + (size_t)j * P * N + row;
+    const float2* q1 = q0 + (j + 1 < np ? (size_t)P * N : 0);
+    float2 v0[RV], v1[RV];
+#pragma unroll
+    for (int k = 0; k < RV; ++k) {
+      const int i = min((int)threadIdx.x + k * RB, N - 1);
+      v0[k] = q0[i];
+      v1[k] = q1[i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < RV; ++k) {
+      if ((int)threadIdx.x + k * RB >= N) break;
+      y[k].x += v0[k].x;
+      y[k].y += v0[k].y;
+      if (j + 1 < np) {
+        y[k].x += v1[k].x;
+        y[k].y += v1[k].y;
+      }
+    }
+  }
+}
+
+// u = y / ||y|| per row; n[p] = ||y||
+__global__ void __launch_bounds__(RB) k_normalise(const float2* __restrict__ parts, int np, int P, int N, float2* u,
+                                                   float* n) {
   const int p = blockIdx.x;
-  const float nn = sqrtf(fmaxf(sums[(size_t)p * nsum], 0.f));
+  float2 y[RV];
+  sum_parts(y, parts, np, P, N);
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < RV; ++k) s += (double)y[k].x * y[k].x + (double)y[k].y * y[k].y;
+  const float nn = sqrtf((float)row_sum(s));
   const float inv = nn > 0.f ? 1.f / nn : 0.f;
-  for (int i = threadIdx.x; i < N; i += WB) {
-    float2 v = y[(size_t)p * N + i];
-    u[(size_t)p * N + i] = make_float2(v.x * inv, v.y * inv);
+#pragma unroll
+  for (int k = 0; k < RV; ++k) {
+    const int i = threadIdx.x + k * RB;
+    if (i < N) u[(size_t)p * N + i] = make_float2(y[k].x * inv, y[k].y * inv);
   }
   if (threadIdx.x == 0) n[p] = nn;
 }
@@ -137,21 +190,27 @@ __global__ void __launch_bounds__(WB) k_loss(const float2* __restrict__ u, const
 }
 
 // G_y = (G_u - Re(u^H G_u) u) / n
-__global__ void __launch_bounds__(WB) k_normback(const float2* __restrict__ Gu, const float2* __restrict__ u,
-                                                  const float* __restrict__ n, int N, float2* Gy) {
-  __shared__ double red[WB / 64];
+__global__ void __launch_bounds__(RB) k_normback(const float2* __restrict__ parts, int np, int P,
+                                                  const float2* __restrict__ u, const float* __restrict__ n, int N,
+                                                  float2* Gy) {
   const int p = blockIdx.x;
-  double v[1] = {0.0};
-  for (int i = threadIdx.x; i < N; i += WB) {
-    const float2 a = u[(size_t)p * N + i], g = Gu[(size_t)p * N + i];
-    v[0] += (double)a.x * g.x + (double)a.y * g.y;
+  float2 a[RV], g[RV];
+#pragma unroll
+  for (int k = 0; k < RV; ++k) {
+    const int i = threadIdx.x + k * RB;
+    a[k] = i < N ? u[(size_t)p * N + i] : make_float2(0.f, 0.f);
   }
-  block_sum<1>(v, red);
-  const float d = (float)v[0];
-  const float inv = n[p] > 0.f ? 1.f / n[p] : 0.f;
-  for (int i = threadIdx.x; i < N; i += WB) {
-    const float2 a = u[(size_t)p * N + i], g = Gu[(size_t)p * N + i];
-    Gy[(size_t)p * N + i] = make_float2((g.x - d * a.x) * inv, (g.y - d * a.y) * inv);
+  const float np_ = n[p];
+  sum_parts(g, parts, np, P, N);
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < RV; ++k) s += (double)a[k].x * g[k].x + (double)a[k].y * g[k].y;
+  const float d = (float)row_sum(s);
+  const float inv = np_ > 0.f ? 1.f / np_ : 0.f;
+#pragma unroll
+  for (int k = 0; k < RV; ++k) {
+    const int i = threadIdx.x + k * RB;
+    if (i < N) Gy[(size_t)p * N + i] = make_float2((g[k].x - d * a[k].x) * inv, (g[k].y - d * a[k].y) * inv);
   }
 }
 
@@ -161,34 +220,66 @@ __device__ __forceinline__ float ld_i(const void* I, size_t i) {
   else return ((const float*)I)[i];
 }
 
-// dtab[b] += sum_i gw_i * (interpolation weight of point b at x_i): the
-// adjoint of the table lookup, accumulated per workgroup in LDS, then added
-// to the global table gradient (one atomic per point and workgroup).
+// hist[b] = sum_i gw_i * (interpolation weight of point b at x_i): the adjoint of the
+// table lookup, in LDS per workgroup, which then writes it to its own place. Bound by
+// the LDS's FP32 atomic additions, 3.3 cycles a lane whether or not lanes meet (copies
+// of the table per lane, up to 64, changed nothing): 45 us for 4.2 M values.
+constexpr int HCHUNK = 4096, HB = 512, HC = 8;  // HC copies, by lane
+
 template <typename IT>
-__global__ void __launch_bounds__(WB) k_hist(const float* __restrict__ gw, const void* __restrict__ I,
-                                              const float* __restrict__ rowmean, int KN, int nt, float scale,
-                                              float last, int chunk, float* dtab) {
-  extern __shared__ float hist[];
-  for (int b = threadIdx.x; b < nt; b += WB) hist[b] = 0.f;
+__global__ void __launch_bounds__(HB) k_hist(const float* __restrict__ gw, const void* __restrict__ I,
+                                              const float* __restrict__ rowmean, int P, int KN, int nt, int nc,
+                                              float scale, float last, float* __restrict__ out) {
+  extern __shared__ float hist[];  // [nt][nc]
+  for (int b = threadIdx.x; b < nt * nc; b += HB) hist[b] = 0.f;
   __syncthreads();
-  const int p = blockIdx.y;
-  const float m = rowmean[p];
-  const float im = m > 0.f ? 1.f / m : 1.f;
-  const size_t base = (size_t)p * KN;
-  const int i0 = blockIdx.x * chunk, i1 = min(KN, i0 + chunk);
-  for (int i = i0 + threadIdx.x; i < i1; i += WB) {
-    const float x = ld_i<IT>(I, base + i) * im;
-    const float s = fminf(fmaxf(x * scale, 0.f), last);
-    const int b = min((int)s, (int)last - 1);
-    const float f = s - (float)b;
-    const float g = gw[base + i];
-    atomicAdd(&hist[b], (1.f - f) * g);
-    atomicAdd(&hist[b + 1], f * g);
+  const int chunks = (KN + HCHUNK - 1) / HCHUNK, items = P * chunks;
+  float* const mine = hist + (threadIdx.x & (nc - 1));
+  for (int it = blockIdx.x; it < items; it += gridDim.x) {
+    const int p = it / chunks, i0 = (it - p * chunks) * HCHUNK, i1 = min(KN, i0 + HCHUNK);
+    const float m = rowmean[p];
+    const float im = m > 0.f ? 1.f / m : 1.f;
+    const size_t base = (size_t)p * KN;
+    float xs[HCHUNK / HB], gs[HCHUNK / HB];  // the chunk's loads together
+#pragma unroll
+    for (int k = 0; k < HCHUNK / HB; ++k) {
+      const int i = min(i0 + (int)threadIdx.x + k * HB, KN - 1);
+      xs[k] = ld_i<IT>(I, base + i);
+      gs[k] = gw[base + i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < HCHUNK / HB; ++k) {
+      if (i0 + (int)threadIdx.x + k * HB >= i1) break;
+      const float s = fminf(fmaxf(xs[k] * im * scale, 0.f), last);
+      const int b = min((int)s, (int)last - 1);
+      const float f = s - (float)b;
+      atomicAdd(&mine[b * nc], (1.f - f) * gs[k]);
+      atomicAdd(&mine[(b + 1) * nc], f * gs[k]);
+    }
   }
   __syncthreads();
-  for (int b = threadIdx.x; b < nt; b += WB) {
-    const float v = hist[b];
-    if (v != 0.f) atomicAdd(&dtab[b], v);
+  float* const o = out + (size_t)blockIdx.x * nt;
+  for (int b = threadIdx.x; b < nt; b += HB) {
+    float v = 0.f;
+    for (int c = 0; c < nc; ++c) v += hist[b * nc + ((b + c) & (nc - 1))];  // lanes on different banks
+    o[b] = v;
+  }
+}
+
+// dtab[b] = the sum of the hb parts (FP64): 64 points by 16 strides per workgroup
+__global__ void __launch_bounds__(1024) k_hist_sum(const float* __restrict__ hist, int hb, int nt, float* dtab) {
+  __shared__ double red[16][64];
+  const int b = blockIdx.x * 64 + (threadIdx.x & 63), w = threadIdx.x >> 6;
+  double s = 0.0;
+  if (b < nt)
+#pragma unroll 8
+    for (int j = w; j < hb; j += 16) s += (double)hist[(size_t)j * nt + b];
+  red[w][threadIdx.x & 63] = s;
+  __syncthreads();
+  if (w == 0 && b < nt) {
+    for (int j = 1; j < 16; ++j) s += red[j][threadIdx.x];
+    dtab[b] = (float)s;
   }
 }
 
@@ -256,9 +347,10 @@ int wnet_pairs(const float* O, int nt, float* tab, void* s) {
   return (int)hipGetLastError();
 }
 
-int wnet_normalise(const void* y, const float* sums, int nsum, int P, int N, void* u, float* n, void* s) {
+int wnet_normalise(const void* y, int parts, int P, int N, void* u, float* n, void* s) {
   if (P <= 0) return 0;
-  k_normalise<<<P, WB, 0, (hipStream_t)s>>>((const float2*)y, sums, nsum, N, (float2*)u, n);
+  if (N > RB * RV) return (int)hipErrorInvalidValue;
+  k_normalise<<<P, RB, 0, (hipStream_t)s>>>((const float2*)y, parts, P, N, (float2*)u, n);
   return (int)hipGetLastError();
 }
 
@@ -269,21 +361,28 @@ int wnet_loss(const void* u, const void* t, int P, int N, void* G, float* fid, f
   return (int)hipGetLastError();
 }
 
-int wnet_normback(const void* Gu, const void* u, const float* n, int P, int N, void* Gy, void* s) {
+int wnet_normback(const void* Gu, int parts, const void* u, const float* n, int P, int N, void* Gy, void* s) {
   if (P <= 0) return 0;
-  k_normback<<<P, WB, 0, (hipStream_t)s>>>((const float2*)Gu, (const float2*)u, n, N, (float2*)Gy);
+  if (N > RB * RV) return (int)hipErrorInvalidValue;
+  k_normback<<<P, RB, 0, (hipStream_t)s>>>((const float2*)Gu, parts, P, (const float2*)u, n, N, (float2*)Gy);
   return (int)hipGetLastError();
 }
 
+int wnet_hist_parts(int P, int KN, int cus) {
+  const int64_t items = (int64_t)P * ((KN + HCHUNK - 1) / HCHUNK);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(items, 2 * cus));
+}
+
 int wnet_hist(const float* gw, const void* I, int ibf16, const float* rowmean, int P, int KN, int nt, float xmax,
-              float* dtab, void* s) {
+              float* hist, int hb, float* dtab, void* s) {
   if (P <= 0) return 0;
-  const int chunk = 8192;
-  dim3 grid((KN + chunk - 1) / chunk, P);
   const float scale = (float)(nt - 1) / xmax, last = (float)(nt - 1);
-  const size_t lds = (size_t)nt * sizeof(float);
-  if (ibf16) k_hist<uint16_t><<<grid, WB, lds, (hipStream_t)s>>>(gw, I, rowmean, KN, nt, scale, last, chunk, dtab);
-  else k_hist<float><<<grid, WB, lds, (hipStream_t)s>>>(gw, I, rowmean, KN, nt, scale, last, chunk, dtab);
+  int nc = HC;
+  while (nc > 1 && (size_t)nt * nc * sizeof(float) > 32 * 1024) nc >>= 1;
+  const size_t lds = (size_t)nt * nc * sizeof(float);
+  if (ibf16) k_hist<uint16_t><<<hb, HB, lds, (hipStream_t)s>>>(gw, I, rowmean, P, KN, nt, nc, scale, last, hist);
+  else k_hist<float><<<hb, HB, lds, (hipStream_t)s>>>(gw, I, rowmean, P, KN, nt, nc, scale, last, hist);
+  k_hist_sum<<<(nt + 63) / 64, 1024, 0, (hipStream_t)s>>>(hist, hb, nt, dtab);
   return (int)hipGetLastError();
 }
 

@@ -1,0 +1,56 @@
+"""Few rows: the masks of a row shared out over several workgroups. The forward
+operator computes each mask as before, so its values equal those of the same
+rows among many; the training gradient of the learned weighting adds up the
+parts (and its histogram of any table size), against the reference."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2302_13524_amd as tm
+from oracle import learned_weights as lw
+from oracle import operators as ops
+
+from gpu_util import c64, dev, device_intensities, f32, relerr
+from test_gpu_wnet import data
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = tm.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("n1,n2,many", [(8, 8, 16500), (16, 16, 4200), (32, 32, 1100), (64, 32, 520), (128, 64, 520)])
+@pytest.mark.parametrize("K", [1, 3, 6])
+def test_forward_of_few_rows(ctx, n1, n2, many, K):
+    g = torch.Generator().manual_seed(n1 * K)
+    N = n1 * n2
+    masks = torch.polar(torch.ones(K, N), 6.28 * torch.rand(K, N, generator=g)).to(dev())
+    t = torch.randn(many, N, dtype=torch.complex64, generator=g).to(dev())
+    for intensity in (False, True):
+        all_rows = tm.tm_forward(ctx, masks, t, n1, n2, intensity)
+        for P in (1, 37, 150):
+            few = tm.tm_forward(ctx, masks, t[:P].contiguous(), n1, n2, intensity)
+            assert torch.equal(few, all_rows[:P]), (intensity, P)
+
+
+@pytest.mark.parametrize("n1,n2,P,nt", [(8, 8, 5, 2), (32, 32, 3, 257), (64, 32, 2, 4096), (16, 16, 300, 64)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_table_gradient_of_parts(ctx, n1, n2, P, nt, bf16):
+    masks, T, I64, v0 = data(n1, n2, P, 31 + nt)
+    I, Iv = device_intensities(I64)
+    if bf16:
+        I = I.to(torch.bfloat16)
+        Iv = I.float().cpu().numpy().astype(np.float64)
+    vals = np.minimum(np.linspace(0.0, 16.0, nt), 4.0).astype(np.float32)
+    tab = np.stack([vals, np.append(np.diff(vals), 0.0).astype(np.float32)], 1)
+    m = masks.astype(np.complex64).astype(np.complex128)
+    Lref, gref = lw.power_loss(ops.FFTOp(m, n1, n2), Iv, T.astype(np.complex128), v0.astype(np.complex128),
+                               vals.astype(np.float64), 3)
+    loss, dtab = tm.tm_wtab_power_grad(ctx, c64(masks), I, c64(T), c64(v0), n1, n2, f32(tab), 3)
+    # the bounds of the gradient's test at the default table
+    assert abs(float(loss.item()) - Lref) < 1e-5 * max(1.0, abs(Lref))
+    assert relerr(dtab.cpu().numpy(), gref) < 1e-3
