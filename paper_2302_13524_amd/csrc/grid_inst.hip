@@ -30,12 +30,45 @@ constexpr bool kWide = wide_compiled(GL1, GL2);
 template <int VAR>
 using Default = std::conditional_t<kWide, WidePlan<kWide ? GL1 : 6, kWide ? GL2 : 6>, Plan<GL1, GL2, -1, VAR>>;
 
+// Up to 2048 waves (two per SIMD) the mixed-axis kernels need no more than two waves'
+// registers, and take the form that loads a mask ahead. Lanczos step / gradient / training
+// backward step, 4 masks, us: 128 x 64, 64 rows 38.9 / 37.9 / 30.5 -> 35.7 / 34.6 / 25.7;
+// 64 x 64, 400 rows 35.3 / 33.7 / 74.0 -> 32.1 / 32.3 / 46.1; 64 x 32, 900 rows 34.6 /
+// 33.7 / 54.3 -> 31.8 / 31.7 / 46.5; 32 x 32, 512 rows 23.2 / 23.6 / 36.4 -> 22.0 / 22.3 /
+// 30.3. Error reduction gains nothing steady (averaged, 64 x 32, 900 rows: 33.9 -> 35.7;
+// cyclic level) and keeps the one form.
+constexpr int FEW_WAVES = 2048;
+
+template <class PLg, typename IT>
+static bool launch_few(int mode, const RowArgs& a, dim3 grid, dim3 block, hipStream_t s) {
+  switch (mode) {
+    case M_GRAD:
+      if (a.sums) row_kernel_few<PLg, M_GRAD, IT, true><<<grid, block, 0, s>>>(a);
+      else row_kernel_few<PLg, M_GRAD, IT, false><<<grid, block, 0, s>>>(a);
+      return true;
+    case M_AGRAD:
+      if (a.sums) row_kernel_few<PLg, M_AGRAD, IT, true><<<grid, block, 0, s>>>(a);
+      else row_kernel_few<PLg, M_AGRAD, IT, false><<<grid, block, 0, s>>>(a);
+      return true;
+    case M_SPEC: row_kernel_few<PLg, M_SPEC, IT><<<grid, block, 0, s>>>(a); return true;
+    case M_LANCZOS: row_kernel_few<PLg, M_LANCZOS, IT><<<grid, block, 0, s>>>(a); return true;
+    case M_LANCZOS_T: row_kernel_few<PLg, M_LANCZOS_T, IT><<<grid, block, 0, s>>>(a); return true;
+    case M_WAPPLY: row_kernel_few<PLg, M_WAPPLY, IT><<<grid, block, 0, s>>>(a); return true;
+    case M_WBACK: row_kernel_few<PLg, M_WBACK, IT><<<grid, block, 0, s>>>(a); return true;
+    default: return false;
+  }
+}
+
 template <class PLg, typename IT>
 static int launch_t(int mode, const RowArgs& a, hipStream_t s) {
   using LC = Launch<PLg>;
   if (a.P <= 0) return 0;
   if (split_mode(mode) && (a.split < 1 || a.split > a.K)) return (int)hipErrorInvalidValue;
   dim3 grid((a.P + LC::RPW - 1) / LC::RPW * (split_mode(mode) ? a.split : 1)), block(LC::WG);
+  if constexpr (PLg::WIDE) {
+    if ((int64_t)grid.x * (LC::WG / 64) <= FEW_WAVES && launch_few<PLg, IT>(mode, a, grid, block, s))
+      return (int)hipGetLastError();
+  }
   switch (mode) {
     case M_FWD_FIELD: row_kernel<PLg, M_FWD_FIELD, IT><<<grid, block, 0, s>>>(a); break;
     case M_FWD_INT: row_kernel<PLg, M_FWD_INT, IT><<<grid, block, 0, s>>>(a); break;

@@ -394,7 +394,9 @@ __device__ __forceinline__ float wtab_eval(const RowArgs& a, float x) {
 // use: there the compiler otherwise loaded and waited for them one at a time
 // (batch sweep over 12 problems 2.60 -> 1.65 ms), while in the inlined kernel
 // the same order costs 5 % (its own schedule overlaps them already).
-template <class PL, int MODE, typename IT, bool SUMS, int WGT, bool OOL = false>
+// FEW: few rows, two waves per SIMD: the row in registers and the next mask's
+// values loaded a mask ahead (the arithmetic is the same).
+template <class PL, int MODE, typename IT, bool SUMS, int WGT, bool OOL = false, bool FEW = false>
 __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>* lds_all, float* red) {
   // Every buffer is in device global memory: the accesses below go through
   // global-address-space pointers, so that where this body is not inlined into
@@ -438,7 +440,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
   // XCD, which its L2 does not keep, 1.26 GB from HBM per Lanczos launch at
   // 2286 x 8192 against 0.6). The cyclic sweep has no accumulator and keeps it
   // all. d (M_LS) is re-read per mask.
-  constexpr int KEEP = (!PL::WIDE || MODE == M_ERC) ? E : (MODE == M_LS || MODE == M_ALS || MODE == M_WBACK) ? 4 : PL::WAVES < 4 && !OOL ? 12 : 8;
+  constexpr int KEEP = (!PL::WIDE || MODE == M_ERC || FEW) ? E : (MODE == M_LS || MODE == M_ALS || MODE == M_WBACK) ? 4 : PL::WAVES < 4 && !OOL ? 12 : 8;
   constexpr bool KEEP_T = KEEP == E;
   C g[E], x[E];
   const C* trow = a.tin + brow * N;
@@ -617,16 +619,17 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
   // 2286 x 8192). The ER and gradient steps load the mask twice and the
   // intensities after the transform: the same changes measured slower there
   // (cyclic ER 0.357 -> 0.376 and 0.413 ms).
-  constexpr bool PF = !PL::WIDE && (MODE == M_SPEC || MODE == M_LANCZOS || MODE == M_LANCZOS_T || MODE == M_WAPPLY);
+  constexpr bool PF = (!PL::WIDE && (MODE == M_SPEC || MODE == M_LANCZOS || MODE == M_LANCZOS_T || MODE == M_WAPPLY)) ||
+                      (FEW && MODE != M_WBACK);
   // Mixed-axis plan: at its 128 registers the compiler waits for each load in
   // turn (Lanczos step 419 us at 2286 x 8192, 294 in groups), so the loads are issued in
   // groups: the mask's and the row's values, then the intensities (loads return
   // in order: these stay in flight during the forward transform), the mask's
   // values for the conjugate multiply half during the inverse transform's last
   // pass and half after it.
-  constexpr bool WI = W && (MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_SPEC || MODE == M_LANCZOS ||
+  constexpr bool WI = W && !PF && (MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_SPEC || MODE == M_LANCZOS ||
                             MODE == M_AGRAD || MODE == M_LANCZOS_T || MODE == M_WAPPLY);
-  constexpr bool WM = WI || (W && (MODE == M_ADJ || MODE == M_BACKPROP || MODE == M_FILT || MODE == M_WBACK));
+  constexpr bool WM = WI || (W && !PF && (MODE == M_ADJ || MODE == M_BACKPROP || MODE == M_FILT || MODE == M_WBACK));
   constexpr int MH = KEEP_T ? E : E / 2;  // of them loaded during that pass
   float icur[PF || WI ? E : 1];
   C mv[PF || WM ? E : 1];  // the mask's values for the conjugate multiply
@@ -1082,6 +1085,15 @@ row_kernel(RowArgs a) {
   __shared__ cx<float> lds_all[Launch<PL>::LDS_ELEMS];
   __shared__ float red[Launch<PL>::RED_FLOATS];
   row_body<PL, MODE, IT, SUMS, Launch<PL>::WG>(a, blockIdx.x, lds_all, red);
+}
+
+// The mixed-axis kernels for few rows (row_body's FEW).
+template <class PL, int MODE, typename IT, bool SUMS = true>
+__global__ void __launch_bounds__(Launch<PL>::WG) __attribute__((amdgpu_waves_per_eu(1, 2)))
+row_kernel_few(RowArgs a) {
+  __shared__ cx<float> lds_all[Launch<PL>::LDS_ELEMS];
+  __shared__ float red[Launch<PL>::RED_FLOATS];
+  row_body<PL, MODE, IT, SUMS, Launch<PL>::WG, false, true>(a, blockIdx.x, lds_all, red);
 }
 
 // The same kernel with an explicit workgroup size WGT (WGT / T rows per

@@ -54,3 +54,29 @@ def test_table_gradient_of_parts(ctx, n1, n2, P, nt, bf16):
     # the bounds of the gradient's test at the default table
     assert abs(float(loss.item()) - Lref) < 1e-5 * max(1.0, abs(Lref))
     assert relerr(dtab.cpu().numpy(), gref) < 1e-3
+
+
+@pytest.mark.parametrize("n1,n2,many", [(32, 32, 2049), (64, 32, 1025), (64, 64, 513), (128, 64, 257)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_few_row_kernels_have_the_same_bits(ctx, n1, n2, many, bf16):
+    # the kernels for few rows (up to many - 1) and for many differ in when they load only
+    g = torch.Generator().manual_seed(many)
+    K, N = 3, n1 * n2
+    masks = torch.polar(torch.ones(K, N), 6.28 * torch.rand(K, N, generator=g)).to(dev())
+    t = torch.randn(many, N, dtype=torch.complex64, generator=g).to(dev())
+    I = tm.tm_forward(ctx, masks, t, n1, n2, True, bf16)
+    s = torch.randn(many, N, dtype=torch.complex64, generator=g).to(dev())
+
+    def run(P):
+        Ip, sp = I[:P].contiguous(), s[:P].contiguous()
+        out = list(tm.tm_gradient(ctx, masks, Ip, sp, n1, n2)) + list(tm.tm_amp_gradient(ctx, masks, Ip, sp, n1, n2))
+        for start in ("lanczos", "spectral"):
+            x = sp.clone()
+            tm.tm_retrieve(ctx, masks, Ip, x, n1, n2,
+                           opts=tm.retrieve_opts(method="er", iters=0, start=start, spectral_iters=5, bf16=bf16))
+            out.append(x)
+        return out
+
+    for P in (1, many - 1):
+        for few, all_rows in zip(run(P), run(many)):
+            assert torch.equal(few, all_rows[:P]), P
