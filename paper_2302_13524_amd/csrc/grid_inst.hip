@@ -35,7 +35,10 @@ using Default = std::conditional_t<kWide, WidePlan<kWide ? GL1 : 6, kWide ? GL2 
 // backward step, 4 masks, us: 128 x 64, 64 rows 38.9 / 37.9 / 30.5 -> 35.7 / 34.6 / 25.7;
 // 64 x 64, 400 rows 35.3 / 33.7 / 74.0 -> 32.1 / 32.3 / 46.1; 64 x 32, 900 rows 34.6 /
 // 33.7 / 54.3 -> 31.8 / 31.7 / 46.5; 32 x 32, 512 rows 23.2 / 23.6 / 36.4 -> 22.0 / 22.3 /
-// 30.3. Error reduction gains nothing steady (averaged, 64 x 32, 900 rows: 33.9 -> 35.7;
+// 30.3. Adjoint, 6 masks: 32 x 32, 64 rows 21.1 -> 16.9, 64 x 32, 900 rows 31.6 -> 30.1; with
+// larger workgroups only to half as many waves (64 x 64, 256 rows 27.0 -> 25.9, 500 rows 33.6
+// -> 34.2). The L-BFGS line sums of 900 rows of 64 x 32, whose prologue has twice the loads
+// in flight, 64 -> 55. Error reduction gains nothing steady (averaged, 64 x 32, 900 rows: 33.9 -> 35.7;
 // cyclic level) and keeps the one form.
 constexpr int FEW_WAVES = 2048;
 
@@ -50,6 +53,12 @@ static bool launch_few(int mode, const RowArgs& a, dim3 grid, dim3 block, hipStr
       if (a.sums) row_kernel_few<PLg, M_AGRAD, IT, true><<<grid, block, 0, s>>>(a);
       else row_kernel_few<PLg, M_AGRAD, IT, false><<<grid, block, 0, s>>>(a);
       return true;
+    case M_ADJ:
+      if (Launch<PLg>::WG > 128 && (int64_t)grid.x * (Launch<PLg>::WG / 64) > FEW_WAVES / 2) return false;
+      row_kernel_few<PLg, M_ADJ, IT><<<grid, block, 0, s>>>(a);
+      return true;
+    case M_LS: row_kernel_few<PLg, M_LS, IT><<<grid, block, 0, s>>>(a); return true;
+    case M_ALS: row_kernel_few<PLg, M_ALS, IT><<<grid, block, 0, s>>>(a); return true;
     case M_SPEC: row_kernel_few<PLg, M_SPEC, IT><<<grid, block, 0, s>>>(a); return true;
     case M_LANCZOS: row_kernel_few<PLg, M_LANCZOS, IT><<<grid, block, 0, s>>>(a); return true;
     case M_LANCZOS_T: row_kernel_few<PLg, M_LANCZOS_T, IT><<<grid, block, 0, s>>>(a); return true;

@@ -296,8 +296,11 @@ __global__ void __launch_bounds__(LWG) k_dir_dots(LbArgs a, double* dots) {
   }
 }
 
-// One wave per row: sums of the slices' partials (fixed order), then lane 0
-// accepts the pending pair, solves, and writes head, count and the coefficients.
+// One wave per row: sums of the slices' partials (fixed order), the pending pair
+// accepted, the small solves, and head, count and the coefficients written. Lane i
+// holds row i of the vectors, so that a solve's step is one division and one
+// multiply-add of all rows; bound by the chain of those steps: 5.9 us for 900 rows (one
+// lane with its vectors in scratch memory: 11.5).
 __global__ void __launch_bounds__(64) k_dir_solve(LbArgs a, const double* dots, int split) {
   __shared__ double tot[NDOT];
   __shared__ double Rm[MMAX * MMAX], Wm[MMAX * MMAX];
@@ -312,20 +315,12 @@ __global__ void __launch_bounds__(64) k_dir_solve(LbArgs a, const double* dots, 
     tot[k] = acc;
   }
   __syncthreads();
-  if (lane != 0) return;
   double* STY = sc + 4;          // [R][R] s_i^T y_j over ring slots
   double* YTY = sc + 4 + R * R;  // [R][R] y_i^T y_j
   double* coef = lb_coef(sc, m);  // cg, cs[R], cy[R]
   const int head0 = (int)sc[0];
   const bool pending = !a.first && sc[3] != 0.0;
   const double* nw = tot;  // s^T y, y^T y, s^T g, y^T g, g^T g of the pending pair
-  double sg[MMAX], yg[MMAX], sy[MMAX], yy[MMAX];
-  for (int j = 0; j < count0; ++j) {
-    sg[j] = tot[5 + 4 * j];
-    yg[j] = tot[6 + 4 * j];
-    sy[j] = tot[7 + 4 * j];
-    yy[j] = tot[8 + 4 * j];
-  }
   // accept the pending pair if s^T y > 0: it becomes the newest stored pair
   // (with m pairs stored, the oldest drops out of the ring)
   const bool acc = pending && nw[0] > 0.0 && isfinite(nw[0]) && nw[1] > 0.0;
@@ -333,60 +328,68 @@ __global__ void __launch_bounds__(64) k_dir_solve(LbArgs a, const double* dots, 
   const int keep = count0 - drop;
   const int k = keep + (acc ? 1 : 0);
   auto oslot = [&](int j) { return (head0 - count0 + j + 2 * R) % R; };
-  for (int i = 0; i < keep; ++i) {
-    for (int j = 0; j < keep; ++j) {
-      Rm[i * MMAX + j] = STY[oslot(drop + i) * R + oslot(drop + j)];
-      Wm[i * MMAX + j] = YTY[oslot(drop + i) * R + oslot(drop + j)];
-    }
-    sg[i] = sg[drop + i];
-    yg[i] = yg[drop + i];
-    sy[i] = sy[drop + i];
-    yy[i] = yy[drop + i];
+  for (int e = lane; e < keep * keep; e += 64) {
+    const int i = e / keep, j = e - i * keep;
+    Rm[i * MMAX + j] = STY[oslot(drop + i) * R + oslot(drop + j)];
+    Wm[i * MMAX + j] = YTY[oslot(drop + i) * R + oslot(drop + j)];
+  }
+  double sg = 0.0, yg = 0.0;  // of this lane's pair
+  if (lane < keep) {
+    sg = tot[5 + 4 * (drop + lane)];
+    yg = tot[6 + 4 * (drop + lane)];
   }
   int head = head0;
   if (acc) {
-    for (int i = 0; i < keep; ++i) {
-      Rm[i * MMAX + keep] = sy[i];
-      Wm[i * MMAX + keep] = Wm[keep * MMAX + i] = yy[i];
-      const int si = oslot(drop + i);
-      STY[si * R + head0] = sy[i];
-      YTY[si * R + head0] = YTY[head0 * R + si] = yy[i];
+    if (lane < keep) {
+      const double sy = tot[7 + 4 * (drop + lane)], yy = tot[8 + 4 * (drop + lane)];
+      Rm[lane * MMAX + keep] = sy;
+      Wm[lane * MMAX + keep] = Wm[keep * MMAX + lane] = yy;
+      const int si = oslot(drop + lane);
+      STY[si * R + head0] = sy;
+      YTY[si * R + head0] = YTY[head0 * R + si] = yy;
+    } else if (lane == keep) {
+      Rm[keep * (MMAX + 1)] = nw[0];
+      Wm[keep * (MMAX + 1)] = nw[1];
+      STY[head0 * R + head0] = nw[0];
+      YTY[head0 * R + head0] = nw[1];
+      sg = nw[2];
+      yg = nw[3];
     }
-    Rm[keep * (MMAX + 1)] = nw[0];
-    Wm[keep * (MMAX + 1)] = nw[1];
-    STY[head0 * R + head0] = nw[0];
-    YTY[head0 * R + head0] = nw[1];
-    sg[keep] = nw[2];
-    yg[keep] = nw[3];
     head = (head0 + 1) % R;
   }
+  __syncthreads();
   // d = -H g = -gam g - S p + gam Y u with R u = S^T g, R^T p = (D + gam Y^T Y) u - gam Y^T g
   const double gg = nw[4];
   double cg = 0.0;
-  double u[MMAX], pv[MMAX];
   bool use = k > 0;
   if (use) {
+    const int li = min(lane, k - 1);  // lanes past the pairs repeat the last row, unread
+    const double rd = Rm[li * (MMAX + 1)];
     const double gam = Rm[(k - 1) * (MMAX + 1)] / Wm[(k - 1) * (MMAX + 1)];
-    for (int i = k - 1; i >= 0; --i) {
-      double t = sg[i];
-      for (int j = i + 1; j < k; ++j) t -= Rm[i * MMAX + j] * u[j];
-      u[i] = t / Rm[i * (MMAX + 1)];
+    double u = 0.0, pv = 0.0, t = sg;
+    for (int j = k - 1; j >= 0; --j) {
+      const double uj = __shfl(t / rd, j, 64);
+      if (lane == j) u = uj;
+      if (lane < j) t -= Rm[li * MMAX + j] * uj;
     }
-    for (int i = 0; i < k; ++i) {
-      double t = Rm[i * (MMAX + 1)] * u[i] - gam * yg[i];
-      for (int j = 0; j < k; ++j) t += gam * Wm[i * MMAX + j] * u[j];
-      for (int j = 0; j < i; ++j) t -= Rm[j * MMAX + i] * pv[j];
-      pv[i] = t / Rm[i * (MMAX + 1)];
-    }
-    double slope = -gam * gg;
-    for (int j = 0; j < k; ++j) slope += -pv[j] * sg[j] + gam * u[j] * yg[j];
-    cg = -gam;
+    t = rd * u - gam * yg;
+    for (int j = 0; j < k; ++j) t += gam * Wm[li * MMAX + j] * __shfl(u, j, 64);
     for (int j = 0; j < k; ++j) {
-      coef[1 + j] = -pv[j];
-      coef[1 + R + j] = gam * u[j];
+      const double pj = __shfl(t / rd, j, 64);
+      if (lane == j) pv = pj;
+      if (lane > j) t -= Rm[j * MMAX + li] * pj;
+    }
+    const double term = -pv * sg + gam * u * yg;
+    double slope = -gam * gg;
+    for (int j = 0; j < k; ++j) slope += __shfl(term, j, 64);
+    cg = -gam;
+    if (lane < k) {
+      coef[1 + lane] = -pv;
+      coef[1 + R + lane] = gam * u;
     }
     if (!(slope < 0.0) || !isfinite(slope)) use = false;  // not a descent direction: drop the history
   }
+  if (lane != 0) return;
   if (!use) {
     // the negative gradient; normalised (unit_first) for the exact line search,
     // whose new iterate does not depend on the direction's scale and whose
@@ -458,6 +461,15 @@ __global__ void __launch_bounds__(LWG) k_step(LbArgs a) {
   const size_t rb = (size_t)p * N;
   double* sc = a.sc + (size_t)p * LB_SCALARS(m);
   const float* s = a.sums + (size_t)p * NSUM;
+  // the row's loads in flight under the step's solve
+  float2 dv[EPT], tv[EPT];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int e = min(tid + i * LWG, N - 1);
+    dv[i] = a.d[rb + e];
+    tv[i] = a.t[rb + e];
+  }
+  __builtin_amdgcn_sched_barrier(0);
   // f(a) = sum (r - 2ab - a^2 c)^2 with sums {r^2, rb, b^2, rc, bc, c^2}
   double c1 = -4.0 * (double)s[1];
   double c2 = 4.0 * (double)s[2] - 2.0 * (double)s[3];
@@ -471,10 +483,8 @@ __global__ void __launch_bounds__(LWG) k_step(LbArgs a) {
   for (int i = 0; i < EPT; ++i) {
     int e = tid + i * LWG;
     if (e >= N) continue;
-    float2 dv = a.d[rb + e];
-    float2 st = make_float2(af * dv.x, af * dv.y);
-    float2 tv = a.t[rb + e];
-    a.t[rb + e] = make_float2(tv.x + st.x, tv.y + st.y);
+    float2 st = make_float2(af * dv[i].x, af * dv[i].y);
+    a.t[rb + e] = make_float2(tv[i].x + st.x, tv[i].y + st.y);
     Sh[e] = st;
   }
   if (tid == 0) {
@@ -518,11 +528,9 @@ __global__ void __launch_bounds__(LWG) k_step_amp(LbArgs a) {
   }
 }
 
-__global__ void k_lb_init(double* sc, int P, int m) {
-  int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= P) return;
-  double* r = sc + (size_t)p * LB_SCALARS(m);
-  for (int i = 0; i < LB_SCALARS(m); ++i) r[i] = 0.0;
+__global__ void __launch_bounds__(64) k_lb_init(double* sc, int m) {
+  double* r = sc + (size_t)blockIdx.x * LB_SCALARS(m);
+  for (int i = threadIdx.x; i < LB_SCALARS(m); i += 64) r[i] = 0.0;
 }
 
 template <int EPT>
@@ -560,7 +568,7 @@ int run_lbfgs(row_launcher fn, const RowArgs& base, int ibf16, int N, int iters,
   const int gmode = amplitude ? M_AGRAD : M_GRAD, lmode = amplitude ? M_ALS : M_LS;
   hipStream_t s = (hipStream_t)stream;
   const int P = base.P;
-  k_lb_init<<<(P + 255) / 256, 256, 0, s>>>((double*)b.sc, P, m);
+  k_lb_init<<<P, 64, 0, s>>>((double*)b.sc, m);
   int e = (int)hipGetLastError();
   if (e) return e;
   void* gcur = b.g;

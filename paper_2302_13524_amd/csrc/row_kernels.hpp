@@ -496,7 +496,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
       const float cg = (float)coef[0];
       const C *lbS = a.lb_S + brow * R * N, *lbY = a.lb_Y + brow * R * N;
       C* dout = a.lb_d + brow * N;
-      constexpr int CH = PL::WIDE ? 8 : E;  // values at a time (their loads' registers)
+      constexpr int CH = PL::WIDE && !FEW ? 8 : E;  // values at a time (their loads' registers)
 #pragma unroll
       for (int c = 0; c < E; c += CH) {
         C dv[CH];
@@ -620,7 +620,8 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
   // intensities after the transform: the same changes measured slower there
   // (cyclic ER 0.357 -> 0.376 and 0.413 ms).
   constexpr bool PF = (!PL::WIDE && (MODE == M_SPEC || MODE == M_LANCZOS || MODE == M_LANCZOS_T || MODE == M_WAPPLY)) ||
-                      (FEW && MODE != M_WBACK);
+                      (FEW && MODE != M_WBACK && MODE != M_LS && MODE != M_ALS && MODE != M_ADJ);
+  constexpr bool AF = FEW && MODE == M_ADJ;  // the next spectrum loaded a mask ahead, the mask under the transform
   // Mixed-axis plan: at its 128 registers the compiler waits for each load in
   // turn (Lanczos step 419 us at 2286 x 8192, 294 in groups), so the loads are issued in
   // groups: the mask's and the row's values, then the intensities (loads return
@@ -638,6 +639,12 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
 #pragma unroll
     for (int i = 0; i < E; ++i) mnext[i] = ld<W>(a.masks + (size_t)m0 * N, at.elem_l(i), at.elem_r(i));
   }
+  C ynext[AF ? E : 1];
+  if constexpr (AF) {
+    const C* y0 = a.yin + brow * a.K * (size_t)N;
+#pragma unroll
+    for (int i = 0; i < E; ++i) ynext[i] = ld<W>(y0, rk + at.freq_l(i), at.freq_r(i));
+  }
   for (int m = m0; m < m1; ++m) {
     if constexpr (!KEEP_T) again = hidden_zero();
     const C* mk = a.masks + (size_t)m * N;
@@ -647,8 +654,14 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
       // spectrum arrives in natural order; place it at the digit-reversed slots
 #pragma unroll
       for (int i = 0; i < E; ++i) {
-        if constexpr (MODE == M_ADJ) x[i] = ld<W>(a.yin + mbase, rk + at.freq_l(i), at.freq_r(i));
+        if constexpr (AF) x[i] = ynext[i];
+        else if constexpr (MODE == M_ADJ) x[i] = ld<W>(a.yin + mbase, rk + at.freq_l(i), at.freq_r(i));
         else x[i] = C{sqrtf(fmaxf(LD_I(i), 0.f)), 0.f};
+      }
+      if constexpr (AF) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) mv[i] = LD_MASK(i);
+        __builtin_amdgcn_sched_barrier(0);
       }
       if (m > 0) fft.fence();
     } else {
@@ -899,6 +912,14 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
           if (more) {
 #pragma unroll
             for (int i = 0; i < E; ++i) mnext[i] = ld<W>(mk1, at.elem_l(i), at.elem_r(i));
+          }
+        });
+      } else if constexpr (AF) {
+        const bool more = m + 1 < m1;
+        fft.inverse(x, [&]() {
+          if (more) {
+#pragma unroll
+            for (int i = 0; i < E; ++i) ynext[i] = ld<W>(a.yin + mbase + N, rk + at.freq_l(i), at.freq_r(i));
           }
         });
       } else if constexpr (WM) {

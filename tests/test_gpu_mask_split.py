@@ -70,6 +70,12 @@ def test_few_row_kernels_have_the_same_bits(ctx, n1, n2, many, bf16):
     def run(P):
         Ip, sp = I[:P].contiguous(), s[:P].contiguous()
         out = list(tm.tm_gradient(ctx, masks, Ip, sp, n1, n2)) + list(tm.tm_amp_gradient(ctx, masks, Ip, sp, n1, n2))
+        y = tm.tm_forward(ctx, masks, sp, n1, n2)
+        out.append(tm.tm_adjoint(ctx, masks, y, n1, n2))
+        for method in ("lbfgs", "lbfgs_amp"):
+            x = sp.clone()
+            tm.tm_retrieve(ctx, masks, Ip, x, n1, n2, opts=tm.retrieve_opts(method=method, iters=3, bf16=bf16))
+            out.append(x)
         for start in ("lanczos", "spectral"):
             x = sp.clone()
             tm.tm_retrieve(ctx, masks, Ip, x, n1, n2,
