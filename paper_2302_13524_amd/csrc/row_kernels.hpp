@@ -619,7 +619,12 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
   // 2286 x 8192). The ER and gradient steps load the mask twice and the
   // intensities after the transform: the same changes measured slower there
   // (cyclic ER 0.357 -> 0.376 and 0.413 ms).
+  // The gradients load ahead on the 16 x 16 grid's plan (200 rows 19.9 -> 17.6 us, 20000
+  // rows 72.0 -> 61.9); with 8 x 8 rows nothing is gained (24.2 -> 26.9 at 20000 rows), and
+  // the large one-axis plans' registers do not hold the values.
+  constexpr bool SMALL = !PL::WIDE && PL::N >= 256 && PL::N <= 512 && (MODE == M_GRAD || MODE == M_AGRAD);
   constexpr bool PF = (!PL::WIDE && (MODE == M_SPEC || MODE == M_LANCZOS || MODE == M_LANCZOS_T || MODE == M_WAPPLY)) ||
+                      SMALL ||
                       (FEW && MODE != M_WBACK && MODE != M_LS && MODE != M_ALS && MODE != M_ADJ);
   constexpr bool AF = FEW && MODE == M_ADJ;  // the next spectrum loaded a mask ahead, the mask under the transform
   // Mixed-axis plan: at its 128 registers the compiler waits for each load in
