@@ -51,6 +51,7 @@ struct RowArgs {
   float* vscale;           // [P] M_SPEC: scale of din (read), of the new previous iterate tin (written)
   void* yout;              // [P][K][N] (M_FWD_*)
   float* sums;             // [P][NSUM]
+  float* fout;             // M_GRAD, M_AGRAD: f written here [P] instead of into sums, or null
   double* sums64;          // [P][2] (M_RES64)
   const float* rowmean;    // [P] mean of I per row (M_SPEC)
   float tau;               // M_SPEC truncation
@@ -1095,7 +1096,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
           gw(a.sums)[prow * NSUM + 0] = out[0];
           gw(a.sums)[prow * NSUM + 1] = out[1];
         } else {
-          gw(a.sums)[prow * NSUM + 0] = out[0];
+          gw(a.fout ? a.fout + prow : a.sums + prow * NSUM)[0] = out[0];
         }
       }
     }

@@ -402,13 +402,8 @@ static int gradient_mode(tm_ctx* c, int mode, tm_dims d, const tm_c32* masks, co
   a.tin = (const tmk::cx<float>*)t;
   a.tout = (tmk::cx<float>*)grad;
   a.sums = sums;
-  r = run_row(c, fn, mode, I_dtype == TM_BF16, a, stream);
-  if (r) return r;
-  if (f) {
-    HIPCHK(c, hipMemcpy2DAsync(f, sizeof(float), sums, tmk::NSUM * sizeof(float), sizeof(float), d.P,
-                               hipMemcpyDeviceToDevice, (hipStream_t)stream));
-  }
-  return TM_OK;
+  a.fout = f;  // by the kernel itself: a copy out of the sums cost the smallest calls a second launch
+  return run_row(c, fn, mode, I_dtype == TM_BF16, a, stream);
 }
 
 static int residual_into(tm_ctx* c, tmk::row_launcher fn, const tm_dims& d, const tm_c32* masks,
