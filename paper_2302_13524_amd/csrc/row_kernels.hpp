@@ -634,8 +634,14 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
   // in order: these stay in flight during the forward transform), the mask's
   // values for the conjugate multiply half during the inverse transform's last
   // pass and half after it.
-  constexpr bool WI = W && !PF && (MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_SPEC || MODE == M_LANCZOS ||
-                            MODE == M_AGRAD || MODE == M_LANCZOS_T || MODE == M_WAPPLY);
+  // One-axis plan of 8192 points (64 x 128): left to itself the compiler saves registers for
+  // a second workgroup per CU that does not fit and waits for each load (error reduction of
+  // 1000 rows 245 us, in groups 173). Where it groups them itself it is left alone.
+  constexpr bool GRP = !W && !OOL && PL::T == 512 && PL::E == 16 &&
+                       (MODE == M_ER || (MODE == M_GRAD && !SUMS) || (MODE == M_AGRAD && (!SUMS || sizeof(IT) == 2)));
+  constexpr bool WI = GRP || (W && !PF && (MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_SPEC ||
+                                           MODE == M_LANCZOS || MODE == M_AGRAD || MODE == M_LANCZOS_T ||
+                                           MODE == M_WAPPLY));
   constexpr bool WM = WI || (W && !PF && (MODE == M_ADJ || MODE == M_BACKPROP || MODE == M_FILT || MODE == M_WBACK));
   constexpr int MH = KEEP_T ? E : E / 2;  // of them loaded during that pass
   float icur[PF || WI ? E : 1];
@@ -683,7 +689,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < E; ++i) x[i] = cmul(TROW(i), mv[i]);
-      } else if constexpr (W) {
+      } else if constexpr (W || GRP) {
         C tv[E - KEEP + 1];
 #pragma unroll
         for (int i = KEEP; i < E; ++i) {

@@ -1,0 +1,44 @@
+"""Grids that keep one FFT axis per pass: the kernels whose loads, LDS layout and
+barriers depend on the size of the row, against the FP64 oracle. Tolerances are
+those of the per-step operators: 1e-5 relative per transform pair in FP32."""
+import pytest
+import torch
+
+import paper_2302_13524_amd as tm
+import tm_synth
+from oracle import operators as ops
+from oracle import retrieval as rt
+
+from gpu_util import c64, device_intensities, problem, relerr, rounded
+
+pytestmark = pytest.mark.gpu
+
+OPTOL = 1e-5
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = tm.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_steps_of_8192_points(ctx, bf16):
+    # 64 x 128: error reduction and both gradients, whose loads go out in groups
+    n1, n2, K, P = 64, 128, 3, 5
+    masks, T, I, _ = problem(n1, n2, K, P, cfg=953, noise=1e4)
+    t0 = T + 0.3 * tm_synth.tm_iid(P, n1 * n2, tm_synth.rng(953, 3))
+    m, t, _ = rounded(masks, t0, I)
+    op = ops.FFTOp(m, n1, n2)
+    Id, Iv = device_intensities(I, bf16)
+    mk, td = c64(masks), c64(t0)
+    for kw, ref in ((dict(), rt.er_step(op, Iv, rt.er_step(op, Iv, t))),
+                    (dict(er_momentum=0.6), rt.er_accelerated(op, Iv, t, 2, 0.6))):
+        tt = td.clone()  # sums only after the last step: both forms of the kernel
+        tm.tm_retrieve(ctx, mk, Id, tt, n1, n2, tm.retrieve_opts("er", iters=2, bf16=bf16, **kw))
+        assert relerr(tt.cpu().numpy(), ref) < 2 * K * OPTOL, kw
+    for grad, ref in ((tm.tm_gradient, rt.intensity_grad), (tm.tm_amp_gradient, rt.amplitude_grad)):
+        g, f = grad(ctx, mk, Id, td, n1, n2)
+        fo, go, _ = ref(op, Iv, t)
+        assert relerr(g.cpu().numpy(), go) < OPTOL and relerr(f.cpu().numpy(), fo) < OPTOL
