@@ -42,3 +42,24 @@ def test_steps_of_8192_points(ctx, bf16):
         g, f = grad(ctx, mk, Id, td, n1, n2)
         fo, go, _ = ref(op, Iv, t)
         assert relerr(g.cpu().numpy(), go) < OPTOL and relerr(f.cpu().numpy(), fo) < OPTOL
+
+
+@pytest.mark.parametrize("n1,n2", [(1, 16), (4, 4), (4, 16), (16, 4), (8, 8), (1, 64), (16, 16), (8, 32), (1, 1024),
+                                   (32, 64), (128, 32), (64, 128)])
+@pytest.mark.parametrize("P", [1, 70])
+def test_masks_in_sequence(ctx, n1, n2, P):
+    # rows from one lane (1 x 16, 4 x 4) to eight waves; every mask's transform follows
+    # another in the same LDS copy: two of a kind (operator), alternating (cyclic sweep)
+    K = 3
+    masks, T, I, _ = problem(n1, n2, K, P, cfg=954, noise=1e4)
+    m, t, Ir = rounded(masks, T, I)
+    op = ops.FFTOp(m, n1, n2)
+    mk, td = c64(masks), c64(T)
+    y = tm.tm_forward(ctx, mk, td, n1, n2)
+    assert relerr(y.cpu().numpy(), op.forward(t)) < OPTOL
+    x = tm.tm_adjoint(ctx, mk, y, n1, n2).cpu().numpy()
+    assert relerr(x, op.adjoint(y.cpu().numpy().astype("complex128"))) < OPTOL
+    tt = td.clone()
+    tm.tm_retrieve(ctx, mk, c64(I).real.contiguous(), tt, n1, n2, tm.retrieve_opts("er_cyclic", iters=1))
+    # K projections, each near the row: those of few points can divide by small fields
+    assert relerr(tt.cpu().numpy(), rt.er_cyclic(m, n1, n2, Ir, t, 1)) < 4 * K * OPTOL
