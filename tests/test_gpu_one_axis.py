@@ -59,6 +59,9 @@ def test_masks_in_sequence(ctx, n1, n2, P):
     assert relerr(y.cpu().numpy(), op.forward(t)) < OPTOL
     x = tm.tm_adjoint(ctx, mk, y, n1, n2).cpu().numpy()
     assert relerr(x, op.adjoint(y.cpu().numpy().astype("complex128"))) < OPTOL
+    rho = tm.tm_residual_f64(ctx, mk, c64(I).real.contiguous(), td, n1, n2).cpu().numpy()
+    # FP64 throughout, of residuals around 1e-2
+    assert relerr(rho, rt.acceptance_residual(op, Ir, t)) < 1e-10
     tt = td.clone()
     tm.tm_retrieve(ctx, mk, c64(I).real.contiguous(), tt, n1, n2, tm.retrieve_opts("er_cyclic", iters=1))
     # K projections, each near the row: those of few points can divide by small fields
