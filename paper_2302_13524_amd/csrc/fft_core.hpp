@@ -508,12 +508,15 @@ __device__ __forceinline__ void inv_from(cx<T>* x, cx<T>* lds, int ltid, const T
 }
 
 // Transforms of one row group: forward() takes x in the layout of the first pass
-// and leaves it in that of the last one, inverse() the other way round.
-template <class PL, typename T>
+// and leaves it in that of the last one, inverse() the other way round. With TWO
+// LDS copies of the row fence() changes to the other one instead of waiting: its
+// last reads were before the barriers of the transform since.
+template <class PL, typename T, bool TWO = false>
 struct LineFft {
-  cx<T>* lds;
+  mutable cx<T>* lds;
   int ltid;
   Tw<T> tw;
+  mutable int to_other = PL::LDS_ROW;
   __device__ __forceinline__ LineFft(cx<T>* l, cx<T>*, int lt, const cx<T>* t1, const cx<T>* t2) : lds(l), ltid(lt), tw(t1, t2) {}
   __device__ __forceinline__ void forward(cx<T>* x) const { fwd_from<PL, 0, T>(x, lds, ltid, tw); }
   template <class H = NoHook>
@@ -521,7 +524,13 @@ struct LineFft {
     inv_from<PL, PL::NP - 1, T>(x, lds, ltid, tw, before_last);
   }
   __device__ __forceinline__ void fence() const {
-    if constexpr (PL::NP > 1) row_barrier<PL>();
+    if constexpr (TWO) {
+      static_assert(PL::NP > 1, "a barrier in each transform");
+      lds += to_other;
+      to_other = -to_other;
+    } else if constexpr (PL::NP > 1) {
+      row_barrier<PL>();
+    }
   }
 };
 

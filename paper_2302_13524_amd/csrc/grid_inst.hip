@@ -68,6 +68,24 @@ static bool launch_few(int mode, const RowArgs& a, dim3 grid, dim3 block, hipStr
   }
 }
 
+// One-axis plan of 8192 points (64 x 128) with at most one row per CU: the second workgroup
+// per CU, for which the kernels with one LDS copy save registers, does not come. Two copies
+// (no barrier between the adjoint's masks) and all registers (the cyclic sweep's loads
+// together) take, few / many rows' kernel: 256 rows, 6 masks, adjoint 45 / 48.6 us, ten sweeps
+// 663 / 683; from the next row on the many rows' kernel wins (1000 rows, 4 masks: 134 / 99,
+// 1725 / 1291).
+template <class PLg, typename IT>
+static bool launch_two(int mode, const RowArgs& a, dim3 grid, dim3 block, hipStream_t s) {
+  switch (mode) {
+    case M_ADJ: row_kernel_few<PLg, M_ADJ, IT><<<grid, block, 0, s>>>(a); return true;
+    case M_ERC:
+      if (a.sums) row_kernel_few<PLg, M_ERC, IT, true><<<grid, block, 0, s>>>(a);
+      else row_kernel_few<PLg, M_ERC, IT, false><<<grid, block, 0, s>>>(a);
+      return true;
+    default: return false;
+  }
+}
+
 template <class PLg, typename IT>
 static int launch_t(int mode, const RowArgs& a, hipStream_t s) {
   using LC = Launch<PLg>;
@@ -77,6 +95,8 @@ static int launch_t(int mode, const RowArgs& a, hipStream_t s) {
   if constexpr (PLg::WIDE) {
     if ((int64_t)grid.x * (LC::WG / 64) <= FEW_WAVES && launch_few<PLg, IT>(mode, a, grid, block, s))
       return (int)hipGetLastError();
+  } else if constexpr (PLg::T == 512) {
+    if ((int)grid.x <= a.cus && launch_two<PLg, IT>(mode, a, grid, block, s)) return (int)hipGetLastError();
   }
   switch (mode) {
     case M_FWD_FIELD: row_kernel<PLg, M_FWD_FIELD, IT><<<grid, block, 0, s>>>(a); break;

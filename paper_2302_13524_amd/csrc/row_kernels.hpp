@@ -71,6 +71,7 @@ struct RowArgs {
   float wtab_last;         // nt - 1
   int out_bf16;            // M_FWD_INT output type
   int add_out;             // M_WBACK: gw is added to yout
+  int cus;                 // CUs of the device
   int split;               // split_mode: workgroups per row (1 .. K), part i the masks [i K / split, (i + 1) K / split)
   const cx<float>* tw32;   // twiddle tables, table of length L at offset L-1
   const cx<double>* tw64;
@@ -349,10 +350,10 @@ __device__ __forceinline__ void st_h(uint16_t* p, int lane, int reg, uint16_t h)
   }
 }
 
-template <class PL, typename T, bool W = PL::WIDE>
-struct FftOf { using type = LineFft<PL, T>; };
-template <class PL, typename T>
-struct FftOf<PL, T, true> { using type = WideFft<PL, T>; };
+template <class PL, typename T, bool TWO, bool W = PL::WIDE>
+struct FftOf { using type = LineFft<PL, T, TWO>; };
+template <class PL, typename T, bool TWO>
+struct FftOf<PL, T, TWO, true> { using type = WideFft<PL, T>; };
 
 // Shape of one workgroup of WGT threads (default: one row of T threads, at
 // least 256 threads; with 32 values per thread at least one wave).
@@ -395,8 +396,9 @@ __device__ __forceinline__ float wtab_eval(const RowArgs& a, float x) {
 // use: there the compiler otherwise loaded and waited for them one at a time
 // (batch sweep over 12 problems 2.60 -> 1.65 ms), while in the inlined kernel
 // the same order costs 5 % (its own schedule overlaps them already).
-// FEW: few rows, two waves per SIMD: the row in registers and the next mask's
-// values loaded a mask ahead (the arithmetic is the same).
+// FEW: few rows, two waves per SIMD (the arithmetic is the same). Mixed-axis plan: the
+// row in registers and the next mask's values loaded a mask ahead. One-axis plan: two LDS
+// copies of the row (one row per workgroup).
 template <class PL, int MODE, typename IT, bool SUMS, int WGT, bool OOL = false, bool FEW = false>
 __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>* lds_all, float* red) {
   // Every buffer is in device global memory: the accesses below go through
@@ -418,7 +420,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
   const int row = blk * RPW + rloc;
   const bool valid = row < a.P;
   const size_t prow = valid ? (size_t)row : 0;
-  const typename FftOf<PL, T>::type fft(lds_all + rloc * PL::LDS_ROW, lds_all + RPW * PL::LDS_ROW, ltid,
+  const typename FftOf<PL, T, FEW>::type fft(lds_all + rloc * PL::LDS_ROW, lds_all + RPW * PL::LDS_ROW, ltid,
                                       a.tw32 + (PL::N1 - 1),
                                       a.tw32 + (PL::N2 - 1));
   const Where<PL> at(ltid);
@@ -626,8 +628,8 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
   constexpr bool SMALL = !PL::WIDE && PL::N >= 256 && PL::N <= 512 && (MODE == M_GRAD || MODE == M_AGRAD);
   constexpr bool PF = (!PL::WIDE && (MODE == M_SPEC || MODE == M_LANCZOS || MODE == M_LANCZOS_T || MODE == M_WAPPLY)) ||
                       SMALL ||
-                      (FEW && MODE != M_WBACK && MODE != M_LS && MODE != M_ALS && MODE != M_ADJ);
-  constexpr bool AF = FEW && MODE == M_ADJ;  // the next spectrum loaded a mask ahead, the mask under the transform
+                      (W && FEW && MODE != M_WBACK && MODE != M_LS && MODE != M_ALS && MODE != M_ADJ);
+  constexpr bool AF = W && FEW && MODE == M_ADJ;  // the next spectrum loaded a mask ahead, the mask under the transform
   // Mixed-axis plan: at its 128 registers the compiler waits for each load in
   // turn (Lanczos step 419 us at 2286 x 8192, 294 in groups), so the loads are issued in
   // groups: the mask's and the row's values, then the intensities (loads return
@@ -1129,11 +1131,12 @@ row_kernel(RowArgs a) {
   row_body<PL, MODE, IT, SUMS, Launch<PL>::WG>(a, blockIdx.x, lds_all, red);
 }
 
-// The mixed-axis kernels for few rows (row_body's FEW).
+// The kernels for few rows (row_body's FEW).
 template <class PL, int MODE, typename IT, bool SUMS = true>
-__global__ void __launch_bounds__(Launch<PL>::WG) __attribute__((amdgpu_waves_per_eu(1, 2)))
+__global__ void __launch_bounds__(Launch<PL>::WG) __attribute__((amdgpu_waves_per_eu(PL::WIDE ? 1 : 2, 2)))
 row_kernel_few(RowArgs a) {
-  __shared__ cx<float> lds_all[Launch<PL>::LDS_ELEMS];
+  static_assert(PL::WIDE || Launch<PL>::RPW == 1, "the second copy follows the workgroup's only row");
+  __shared__ cx<float> lds_all[(PL::WIDE ? 1 : 2) * Launch<PL>::LDS_ELEMS];
   __shared__ float red[Launch<PL>::RED_FLOATS];
   row_body<PL, MODE, IT, SUMS, Launch<PL>::WG, false, true>(a, blockIdx.x, lds_all, red);
 }

@@ -194,6 +194,7 @@ tmk::RowArgs base_args(tm_ctx* c, const tm_dims& d, const tm_c32* masks) {
   memset(&a, 0, sizeof a);
   a.P = d.P;
   a.K = d.K;
+  a.cus = c->cus;
   a.split = mask_split(c, d);
   a.masks = (const tmk::cx<float>*)masks;
   a.tw32 = c->tw32;

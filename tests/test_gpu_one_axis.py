@@ -9,7 +9,7 @@ import tm_synth
 from oracle import operators as ops
 from oracle import retrieval as rt
 
-from gpu_util import c64, device_intensities, problem, relerr, rounded
+from gpu_util import c64, dev, device_intensities, problem, relerr, rounded
 
 pytestmark = pytest.mark.gpu
 
@@ -66,3 +66,22 @@ def test_masks_in_sequence(ctx, n1, n2, P):
     tm.tm_retrieve(ctx, mk, c64(I).real.contiguous(), tt, n1, n2, tm.retrieve_opts("er_cyclic", iters=1))
     # K projections, each near the row: those of few points can divide by small fields
     assert relerr(tt.cpu().numpy(), rt.er_cyclic(m, n1, n2, Ir, t, 1)) < 4 * K * OPTOL
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_few_rows_of_8192_points_have_the_same_bits(ctx, bf16):
+    # 64 x 128: up to one row per CU the adjoint and the cyclic sweep run with two LDS copies
+    n1, n2, K = 64, 128, 3
+    few = torch.cuda.get_device_properties(0).multi_processor_count
+    g = torch.Generator().manual_seed(955)
+    masks = torch.polar(torch.ones(K, n1 * n2), 6.28 * torch.rand(K, n1 * n2, generator=g)).to(dev())
+    T = torch.randn(few + 1, n1 * n2, dtype=torch.complex64, generator=g).to(dev())
+    y = tm.tm_forward(ctx, masks, T, n1, n2)
+    Id = (y.abs() ** 2).to(torch.bfloat16 if bf16 else torch.float32)
+    x = tm.tm_adjoint(ctx, masks, y, n1, n2)
+    assert torch.equal(tm.tm_adjoint(ctx, masks, y[:few].contiguous(), n1, n2), x[:few])
+    o = tm.retrieve_opts("er_cyclic", iters=2, bf16=bf16)
+    many, t = T + 0.1, (T + 0.1)[:few].contiguous()
+    tm.tm_retrieve(ctx, masks, Id, many, n1, n2, o)
+    tm.tm_retrieve(ctx, masks, Id[:few].contiguous(), t, n1, n2, o)
+    assert torch.equal(t, many[:few])
