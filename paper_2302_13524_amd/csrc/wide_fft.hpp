@@ -11,13 +11,14 @@
 // Every element index is a set of bits (axis 2 low, axis 1 above); a pass
 // assigns four of them to the register number and the others to the thread.
 // Inside a digit the radix-2 decimation-in-time stages with a factor w other
-// than a quarter turn take six fused multiply-adds: a + w b in two per
-// component, a - w b = 2 a - (a + w b) in one. The twiddles between digits stay
-// separate products: taken along in the stages a launch is 3 to 8 % shorter,
-// but its error against 64 bits is larger than the one-axis plans' (a residual
-// 2.1e-6 off instead of 1.7e-6; now 1.7e-6 or less).
+// than a quarter turn take six operations per butterfly (bfly). The twiddles
+// between digits stay separate products: taken along in the stages a launch is
+// 3 to 8 % shorter, but its error against 64 bits was larger than the one-axis
+// plans' (a residual 2.1e-6 off instead of 1.7e-6).
 #pragma once
 #include "fft_core.hpp"
+
+#include <type_traits>
 
 namespace tmk {
 
@@ -190,36 +191,41 @@ struct WidePlan {
 };
 
 // --------------------------------------------------------------- butterflies
-// W_16^k = exp(-2 pi j k / 16), k = 1 .. 3, for the stages of a digit. In FP32 the
-// nearest values of its cosines are all too small (|w| = 1 - 1.7e-8 for k = 2,
-// 1 - 2.9e-8 for k = 1 and 3): with them alone every transform loses that much
-// gain, which moves a residual more than its random rounding does. Half of the
-// factors therefore take the next value up in one component, so that the gains
-// cancel in the mean (they come to +0.4e-8 and -0.1e-8).
-template <typename T, bool UP>
-constexpr cx<T> w16c(int k) {
-  constexpr bool f = sizeof(T) == 4;
-  constexpr T c = T(0.92387953251128673848), s = T(0.38268343236508977173), r = T(0.70710678118654752440);
-  constexpr T cu = f ? T(0.92387956380844116211) : c, ru = f ? T(0.70710682868957519531) : r;
-  return k == 1 ? cx<T>{c, -s} : k == 3 ? cx<T>{s, -cu} : cx<T>{r, UP ? -ru : -r};
-}
-
-// a, b <- a + w b, a - w b with w (INV: conj w), times -j (INV: +j) when ROT
-template <bool INV, bool ROT, typename T>
-__device__ __forceinline__ void bfly(cx<T>& a, cx<T>& b, cx<T> w) {
-  const T wy = INV ? -w.y : w.y;
-  T px, py, qx, qy;  // (w b).x = px b.x - py b.y, (w b).y = qx b.y + qy b.x
-  if constexpr (!ROT) {
-    px = w.x; py = wy; qx = w.x; qy = wy;
-  } else if constexpr (!INV) {  // -j w = (w.y, -w.x)
-    px = wy; py = -w.x; qx = wy; qy = -w.x;
-  } else {  // +j w = (-w.y, w.x)
-    px = -wy; py = w.x; qx = -wy; qy = w.x;
+// a, b <- a + w b, a - w b with w = W_16^K = exp(-2 pi j K / 16), K = 1 .. 3 (INV: conj w),
+// times -j (INV: +j) when ROT. w b = c u with c = cos(pi / 8), or sqrt(1/2) for K = 2, and
+// u = b's components with the tangent tan(pi / 8), or 1, between them: two operations for u
+// and one fused multiply-add per result and component, each of which rounds its own value
+// once (Linzer and Feig's form for fused multiply-add machines; the difference as
+// 2 a - (a + w b), of the same length, takes over the sum's rounding). Error of a transform
+// against 64 bits, rms, forward / inverse, 1e-7: 128 x 64 1.204 / 1.206, one axis per pass
+// 1.235 / 1.234, differences from the sums 1.268 / 1.267; 32 x 32 1.043 / 1.052, 1.064 / 1.060,
+// 1.103 / 1.105.
+//
+// In FP32 the nearest values of both c are too small (by 3.1e-8 and 1.7e-8): with them alone
+// every transform loses that much gain (-4.5e-8 at 128 x 64), which moves a residual more
+// than its random rounding does. Half of the butterflies therefore take the next value up (of
+// sqrt(1/2) in one component, as it lies further off), and the gain comes to -0.8e-8. Of the
+// ways to choose the half this has the least error over the four grids, by 0.1 to 0.8 %.
+template <int K, bool INV, bool ROT, typename T>
+__device__ __forceinline__ void bfly(cx<T>& a, cx<T>& b) {
+  constexpr bool up = sizeof(T) == 4 && ROT == (K != 1);
+  constexpr T t = T(0.41421356237309504880), r = T(0.70710678118654752440), c1 = T(0.92387953251128673848);
+  constexpr T cx_ = K == 2 ? r : up ? T(0.92387956380844116211) : c1;
+  constexpr T cy = K == 2 ? (up ? T(0.70710682868957519531) : r) : cx_;
+  T ux, uy;
+  if constexpr (K == 1) {
+    ux = fmadd(INV ? -t : t, b.y, b.x);
+    uy = fmadd(INV ? t : -t, b.x, b.y);
+  } else if constexpr (K == 2) {
+    ux = INV ? b.x - b.y : b.x + b.y;
+    uy = INV ? b.y + b.x : b.y - b.x;
+  } else {
+    ux = fmadd(t, b.x, INV ? -b.y : b.y);
+    uy = fmadd(t, b.y, INV ? b.x : -b.x);
   }
-  const T sx = fmadd(-py, b.y, fmadd(px, b.x, a.x));
-  const T sy = fmadd(qy, b.x, fmadd(qx, b.y, a.y));
-  b = cx<T>{fmadd(T(2), a.x, -sx), fmadd(T(2), a.y, -sy)};
-  a = cx<T>{sx, sy};
+  const T vx = !ROT ? ux : INV ? -uy : uy, vy = !ROT ? uy : INV ? ux : -ux;
+  b = cx<T>{fmadd(-cx_, vx, a.x), fmadd(-cy, vy, a.y)};
+  a = cx<T>{fmadd(cx_, vx, a.x), fmadd(cy, vy, a.y)};
 }
 // the same for w = 1
 template <bool INV, bool ROT, typename T>
@@ -255,8 +261,15 @@ __device__ __forceinline__ void dit_stage(cx<T>* u) {
         bfly1<INV, false, T>(v[0], v[h]);
         if constexpr (m >= 4) bfly1<INV, true, T>(v[q], v[q + h]);
       } else {
-        bfly<INV, false, T>(v[k], v[k + h], w16c<T, true>(k * (16 / m)));
-        bfly<INV, true, T>(v[k + q], v[k + q + h], w16c<T, false>(k * (16 / m)));
+        auto turn = [&](auto n) {
+          bfly<decltype(n)::value, INV, false, T>(v[k], v[k + h]);
+          bfly<decltype(n)::value, INV, true, T>(v[k + q], v[k + q + h]);
+        };
+        switch (k * (16 / m)) {  // a constant of the unrolled loop
+          case 1: turn(std::integral_constant<int, 1>{}); break;
+          case 2: turn(std::integral_constant<int, 2>{}); break;
+          default: turn(std::integral_constant<int, 3>{}); break;
+        }
       }
     }
   }
