@@ -182,15 +182,18 @@ __global__ void __launch_bounds__(256, 2) k_cgemm_mfma(CgemmArgs g) {
 // The same product on the BF16 matrix cores (16 times the FP32 rate). Every FP32
 // value is the exact sum of three BF16 values, each the nearest to what the ones
 // before it leave,
-//   x = x1 + x2 + x3,  |x2| <= 2^-8 |x|,  |x3| <= 2^-16 |x|,
-// and a b = a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a3 b1 + a2 b2): six products that the
-// FP32 sums take in exactly; what is left out is below 2^-23 of the product and of
-// either sign. The BF16 cores cut off what falls below the accumulator's last place,
-// so that a long chain of one sign comes out short (by 1.6e-6 over 8192 k): the six
-// products of 8 complex k are summed by themselves, the smallest first, and added to
-// the total by a rounding FP32 add. Error against 64 bits, largest over sum |a||b|:
-// 2286 x 2286 x 8192 normal values 6.4e-8 (FP32 cores 2.5e-7), conj(A) A^T of unit
-// phases, whose diagonal is one sign, 5.4e-8 (2.3e-7).
+//   x = x1 + x2 + x3,  |x2| <= 2^-8 |x|,  |x3| <= 2^-17 |x|,
+// and a b = a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1) + (a2 b3 + a3 b2): eight
+// products that the FP32 sums take in exactly; a3 b3, at most 2^-34 of a b, is left
+// out. The BF16 cores cut off what falls below the accumulator's last place, so that a
+// long chain of one sign comes out short (by 1.6e-6 over 8192 k): of 16 complex k the
+// products a1 b1 are summed by themselves, the others by themselves, and the rounded sum
+// of the two is added to the total. A sum of one product then comes out as FP32 rounds
+// it: largest error 5.9e-8 of the product, rms 2.5e-8, as on the FP32 cores (with a1 b1
+// in the others' chain and without the last two products 1.3e-7 and 3.5e-8). Longer
+// sums, largest error over sum |a||b| (FP32 cores): 8192 k of normal values 3.8e-8
+// (2.3e-7), 64 of one sign 1.7e-7 (5.7e-7), unit phases times their conjugates 3.0e-8
+// (1.8e-7).
 //
 // Real embedding as above over k = (re, im) pairs; the operand for C_r flips
 // the imaginary parts' signs, the one for C_i swaps each pair.
@@ -203,8 +206,8 @@ __global__ void __launch_bounds__(256, 2) k_cgemm_mfma(CgemmArgs g) {
 // has 648 of them for 768 places, where 128 x 128 tiles at two per CU would leave a
 // third of the chip idle. The operands are split while they are staged, so nothing
 // is read twice and no workspace is kept; B is stored once for C_r and once for C_i.
-// 2335 us at 2286 x 2286 x 8192 (FP32 cores 4456): 880 TFLOP/s of BF16 products, with
-// the splitting (VALU) about as long as the products and beside them.
+// 2588 us at 2286 x 2286 x 8192 (FP32 cores 4361): 1060 TFLOP/s of BF16 products, with
+// the splitting (VALU) beside them.
 constexpr int SN = 64;                                        // tile columns
 constexpr int S_PLANE_A = TM * TK, S_PLANE_B = SN * TK;  // words (two BF16) of a plane
 
@@ -387,35 +390,38 @@ __global__ void __launch_bounds__(256, 3) k_cgemm_split(CgemmArgs g) {
       return;
     }
     if (k0 + TK < g.K) load(k0 + TK);
+    // one 32 x 32 block and part after the other, so that its two sums are the only ones beside
+    // the total's (168 VGPRs): two blocks at a time spill, 2.9 ms against 2.6
+    auto fragA = [&](int p, int i, int k16) {
+      const int at = chunk_at(wm + 32 * i + (lane & 31), 2 * k16 + (lane >> 5));
+      return as_bf16(*(const u32x4*)(sA + p * S_PLANE_A + 4 * at));
+    };
+    auto fragB = [&](int part, int p, int k16) {
+      const int at = chunk_at(wn + (lane & 31), 2 * k16 + (lane >> 5));
+      return as_bf16(*(const u32x4*)(sB + (3 * part + p) * S_PLANE_B + 4 * at));
+    };
 #pragma unroll
-    for (int k16 = 0; k16 < 2; ++k16) {
-      const int c = 2 * k16 + (lane >> 5);
-      bf16x8_t b[2][3];
-#pragma unroll
-      for (int part = 0; part < 2; ++part)
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-          b[part][p] = as_bf16(*(const u32x4*)(sB + (3 * part + p) * S_PLANE_B + 4 * chunk_at(wn + (lane & 31), c)));
+    for (int part = 0; part < 2; ++part)
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        bf16x8_t a[3];
+        f32x16 low = {}, high = {};
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
-          a[p] = as_bf16(*(const u32x4*)(sA + p * S_PLANE_A + 4 * chunk_at(wm + 32 * i + (lane & 31), c)));
+        for (int k16 = 0; k16 < 2; ++k16) {
+          bf16x8_t a[3], b[3];
 #pragma unroll
-        for (int part = 0; part < 2; ++part) {
-          f32x16 t = {};
+          for (int p = 0; p < 3; ++p) a[p] = fragA(p, i, k16), b[p] = fragB(part, p, k16);
 #pragma unroll
-          for (int lev = 2; lev >= 0; --lev)
+          for (int lev = 3; lev >= 1; --lev)
 #pragma unroll
-            for (int p = lev; p >= 0; --p)
-              t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[lev - p], b[part][p], t, 0, 0, 0);
-          f32x16& to = part ? ci[i][0] : cr[i][0];
-#pragma unroll
-          for (int e = 0; e < 16; ++e) to[e] += t[e];
+            for (int p = min(lev, 2); p >= max(lev - 2, 0); --p)
+              low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[lev - p], b[p], low, 0, 0, 0);
+          high = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], high, 0, 0, 0);
         }
+        f32x16& to = part ? ci[i][0] : cr[i][0];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) to[e] += high[e] + low[e];
+        __builtin_amdgcn_sched_barrier(0);
       }
-    }
   }
   store_tile<1>(g, cr, ci, m0 + wm, n0 + wn);
 }
