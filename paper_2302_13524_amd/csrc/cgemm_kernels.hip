@@ -43,6 +43,7 @@ struct CgemmArgs {
   int64_t ldc;
   int conj_c;   // store conj(C)
   int veca, vecb;  // 16-byte loads of two complex values allowed
+  int range;       // largest sum of the (biased) exponents of A's and B's staged magnitudes
 };
 
 // The (16 VPT) x TK complex values of an operand's tile in registers, VPT per thread.
@@ -96,9 +97,9 @@ __device__ __forceinline__ void stage_store(float2* lds, const Stage<VPT>& s) {
 // 8 q + 4 (lane / 32) + r for element 4 q + r
 template <int NJ>
 __device__ __forceinline__ void store_tile(const CgemmArgs& g, const f32x16 (&cr)[2][NJ], const f32x16 (&ci)[2][NJ], int m0,
-                                           int n0) {
+                                           int n0, float scale = 1.f) {
   const int lane = threadIdx.x & 63;
-  const float sgn = g.conj_c ? -1.f : 1.f;
+  const float sgn = g.conj_c ? -scale : scale;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -108,7 +109,7 @@ __device__ __forceinline__ void store_tile(const CgemmArgs& g, const f32x16 (&cr
         const int m = m0 + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
         const int n = n0 + 32 * j + (lane & 31);
         const float x = cr[i][j][e], y = ci[i][j][e];
-        if (m < g.M && n < g.N) g.C[(int64_t)m * g.ldc + n] = make_float2(x, sgn * y);
+        if (m < g.M && n < g.N) g.C[(int64_t)m * g.ldc + n] = make_float2(scale * x, sgn * y);
       }
 }
 
@@ -198,9 +199,16 @@ __global__ void __launch_bounds__(256, 2) k_cgemm_mfma(CgemmArgs g) {
 // Real embedding as above over k = (re, im) pairs; the operand for C_r flips
 // the imaginary parts' signs, the one for C_i swaps each pair.
 //
-// Values outside [2^-48, 2^48] (0 apart) could take a small product below the
-// normal range, and infinities and NaN do not split; the tile sees either while
-// it stages them, stops, and is left to k_cgemm_redo.
+// The operands are scaled by 2^24 each, so that every part of every FP32 value,
+// subnormal ones too, is a normal number; a product that all the same falls below the
+// normal range is then below 2^-174 of the result's scale, where FP32 itself ends at
+// 2^-149. At the other end the largest magnitudes of a tile's rows and columns may have a
+// product up to 2^76 / K (2^63 at 8192 k), so that no sum overflows. Above it, and with
+// infinities, the tile stops as soon as it has staged such a value and is left to
+// k_cgemm_redo (a NaN gives NaN in its row or column either way). With a range per value
+// in place of the scaling, [2^-48, 2^48], one sine of pi in a row of phases sent its tiles
+// there: 2286 x 2286 x 8192 with phases of 0 and pi took 4390 us, so
+// 2404.
 //
 // 128 x 64 tiles and three workgroups per CU (168 VGPRs, 48 KB of LDS): 2286 x 2286
 // has 648 of them for 768 places, where 128 x 128 tiles at two per CU would leave a
@@ -237,19 +245,14 @@ __device__ __forceinline__ void split2(float a, float b, unsigned& p1, unsigned&
   p3 = pack_bf16(a3, b3);
 }
 
-// range of the nonzero magnitudes seen, as bit patterns (zero counts as largest for lo)
-struct Seen {
-  unsigned lo = 0xffffffffu;
-  int hi = 0;
-  __device__ __forceinline__ void add(float a, float b) {
-    const unsigned ua = __float_as_uint(a) & 0x7fffffffu, ub = __float_as_uint(b) & 0x7fffffffu;
-    hi = max(hi, max((int)ua, (int)ub));
-    lo = min(lo, min(ua - 1u, ub - 1u));
-  }
-  __device__ __forceinline__ bool splits() const {
-    return (hi == 0 || lo >= (79u << 23) - 1u) && hi <= (int)(175u << 23);  // 2^-48, 2^48
-  }
-};
+constexpr float UP = 0x1p24f, DOWN = 0x1p-48f;  // on the operands while they are staged, on the result
+constexpr float SEEN = 0x1p44f;                 // (staged) magnitudes below it are not published
+constexpr int SEEN_BITS = (127 + 44) << 23;
+
+// the tile's largest magnitude of an operand, as a bit pattern in LDS
+__device__ __forceinline__ void publish(int& most, float seen) {
+  if (seen > SEEN && __float_as_int(seen) > most) atomicMax(&most, __float_as_int(seen));
+}
 
 // One unit: four complex k of one row (a 16-byte chunk of each plane). A thread
 // stages two units of A and one of B per step. Rows past the end repeat the last
@@ -292,13 +295,14 @@ __device__ __forceinline__ void unit_tail(Unit& u, int left) {
 // A unit into its three LDS planes (chunk index of the unit, words of a plane); B's
 // for C_r and, three planes on, for C_i
 template <bool isB>
-__device__ __forceinline__ void split_store(unsigned* lds, int plane, int chunk, const Unit& u, Seen& seen) {
+__device__ __forceinline__ void split_store(unsigned* lds, int plane, int chunk, const Unit& u, float& seen) {
   u32x4 w[3];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     unsigned x, y, z;
-    seen.add(u.v[i].x, u.v[i].y);
-    split2(u.v[i].x, u.v[i].y, x, y, z);
+    const float re = UP * u.v[i].x, im = UP * u.v[i].y;
+    seen = fmaxf(fmaxf(seen, fabsf(re)), fabsf(im));
+    split2(re, im, x, y, z);
     w[0][i] = x, w[1][i] = y, w[2][i] = z;
   }
 #pragma unroll
@@ -332,13 +336,13 @@ constexpr unsigned REDO = 0x7fc5a5a5u;
 template <bool BK>
 __global__ void __launch_bounds__(256, 3) k_cgemm_split(CgemmArgs g) {
   __shared__ __attribute__((aligned(16))) unsigned lds[3 * (S_PLANE_A + 2 * S_PLANE_B)];
-  __shared__ int bad;
+  __shared__ int most[2];  // of A, of B
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * 32;
   const int m0 = blockIdx.y * TM, n0 = blockIdx.x * SN;
   unsigned* const sA = lds;
   unsigned* const sB = lds + 3 * S_PLANE_A;
-  if (tid == 0) bad = 0;
+  if (tid < 2) most[tid] = SEEN_BITS;
   f32x16 cr[2][1], ci[2][1];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -357,7 +361,7 @@ __global__ void __launch_bounds__(256, 3) k_cgemm_split(CgemmArgs g) {
   const float2* const pA = g.A + (int64_t)m0 * g.lda;
   const float2* const pB = g.B + (BK ? (int64_t)n0 * g.ldb : n0);
   Unit ra0, ra1, rb;
-  Seen seen;
+  float seenA = 0.f, seenB = 0.f;
   auto load = [&](int k0) {
     const auto A = buffer_of(pA + k0, ((int64_t)rows * g.lda + g.K - k0) * 8);
     const auto B = BK ? buffer_of(pB + k0, ((int64_t)cols * g.ldb + g.K - k0) * 8)
@@ -380,12 +384,14 @@ __global__ void __launch_bounds__(256, 3) k_cgemm_split(CgemmArgs g) {
       unit_tail(ra1, g.K - k0 - 4 * kuA);
       unit_tail(rb, g.K - k0 - 4 * kuB);
     }
-    split_store<false>(sA, S_PLANE_A, chunk_at(tid >> 2, kuA), ra0, seen);
-    split_store<false>(sA, S_PLANE_A, chunk_at((tid >> 2) + 64, kuA), ra1, seen);
-    split_store<true>(sB, S_PLANE_B, chunk_at(rB, kuB), rb, seen);
-    if (!seen.splits()) bad = 1;
+    split_store<false>(sA, S_PLANE_A, chunk_at(tid >> 2, kuA), ra0, seenA);
+    split_store<false>(sA, S_PLANE_A, chunk_at((tid >> 2) + 64, kuA), ra1, seenA);
+    split_store<true>(sB, S_PLANE_B, chunk_at(rB, kuB), rb, seenB);
+    publish(most[0], seenA);
+    publish(most[1], seenB);
     __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(bad)) {  // next written behind the next barrier
+    // (next written behind the next barrier)
+    if (__builtin_amdgcn_readfirstlane((most[0] >> 23) + (most[1] >> 23)) > g.range) {
       if (tid == 0) g.C[(int64_t)m0 * g.ldc + n0].x = __uint_as_float(REDO);
       return;
     }
@@ -423,7 +429,7 @@ __global__ void __launch_bounds__(256, 3) k_cgemm_split(CgemmArgs g) {
         __builtin_amdgcn_sched_barrier(0);
       }
   }
-  store_tile<1>(g, cr, ci, m0 + wm, n0 + wn);
+  store_tile<1>(g, cr, ci, m0 + wm, n0 + wn, DOWN);
 }
 
 // the tiles that the split could not take
@@ -459,6 +465,10 @@ int launch_cgemm(int M, int N, int K, const void* A, int64_t lda, const void* B,
   g.conj_c = conj_c;
   g.veca = lda % 2 == 0 && (uintptr_t)A % 16 == 0;
   g.vecb = ldb % 2 == 0 && (uintptr_t)B % 16 == 0;
+  // sums of 2 K products of values up to 2^(e + 1) stay below 2^127
+  int lg = 0;
+  while ((1ll << lg) < K) ++lg;
+  g.range = 127 - 3 - lg + 2 * 127;
   // 32-bit offsets inside a tile's rows
   if (K >= SPLIT_K && lda < (1 << 20) && ldb < (1 << 20)) {
     const dim3 grid((N + SN - 1) / SN, (M + TM - 1) / TM);

@@ -76,3 +76,38 @@ def test_long_sum_of_one_sign_is_not_short(ctx):
     short = np.mean((ref - C.real) / ref)
     print(f"mean shortfall {short:.2e}, largest {np.max(np.abs(C.real - ref) / ref):.2e}", flush=True)
     assert abs(short) < 2.0**-23
+
+
+@pytest.mark.parametrize("value", [1e-15, 1e-30, 1e-42, 2.0**27, np.nan])
+def test_other_rows_do_not_see_a_value_out_of_range(ctx, value):
+    # values far below the others (a sine of pi, subnormal ones), or large, or NaN, keep the
+    # tile on its path: the bits of every other row and column stay
+    g = np.random.default_rng(11)
+
+    def rnd(*s):
+        return (g.standard_normal(s) + 1j * g.standard_normal(s)).astype(np.complex64)
+
+    A, B = rnd(100, 90), rnd(60, 90)
+    C = _product(ctx, A, B)
+    A[7, 88] = value
+    B[9, 3] = value * 1j
+    got = _product(ctx, A, B)
+    keep = np.ones(C.shape, bool)
+    keep[7] = keep[:, 9] = False
+    assert np.array_equal(got[keep], C[keep])
+
+
+@pytest.mark.parametrize("ea,eb", [(-40, -40), (-100, 10), (10, -100), (-60, -64), (-140, 60), (60, -140), (-70, -75),
+                                   (30, 30), (90, -50), (60, 50)])
+def test_single_products_of_any_scale(ctx, ea, eb):
+    # A's and B's values around 2^ea and 2^eb, subnormal ones among them, beside others near
+    # one; products down to FP32's subnormal numbers (steps of 2^-149)
+    g = np.random.default_rng(12)
+    M, N, K = 130, 70, 64
+    A = np.zeros((M, K), np.complex64)
+    A[np.arange(M), np.arange(M) % K] = np.ldexp((1 + g.random(M)).astype(np.float32), ea)
+    B = np.ldexp((1 + g.random((N, K))).astype(np.float32), eb).astype(np.complex64)
+    A[::3, :] = A[::3, :] != 0
+    C = _product(ctx, A, B).real.astype(np.float64)
+    ref = A.real.astype(np.float64) @ B.real.astype(np.float64).T
+    assert np.all(np.abs(C - ref) <= 2.0**-24 * (1 + 2.0**-8) * np.abs(ref) + 2.0**-149)
