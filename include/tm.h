@@ -250,13 +250,20 @@ int tm_set_variant(tm_ctx *ctx, int32_t n1, int32_t n2, int32_t variant);
  * rows only where a workgroup stays at 512 threads or fewer).
  * On those grids configurations 0 and 1 run kernels whose FFT passes mix both
  * axes (one row of N/16 threads per workgroup, of both digit orders the same);
- * their tm_config_info entry is the shape of the one-axis kernels.
+ * their tm_config_info entry is the shape of the one-axis kernels, that of the
+ * kernels which run is told by tm_config_kernel.
  *
  * tm_config_info: 1 if configuration cfg is compiled for the grid, with its
  * threads per workgroup, rows per workgroup and values per thread (each
  * pointer may be NULL); 0 otherwise. No device work. */
 int tm_config_info(int32_t n1, int32_t n2, int32_t cfg, int32_t *wg, int32_t *rows_per_wg,
                    int32_t *values_per_thread);
+/* The kernels that configuration cfg runs: the lowest configuration that runs the
+ * same ones (-1 if cfg is not compiled for the grid), with their threads per
+ * workgroup, rows per workgroup and values per thread (each pointer may be NULL).
+ * No device work. */
+int tm_config_kernel(int32_t n1, int32_t n2, int32_t cfg, int32_t *wg, int32_t *rows_per_wg,
+                     int32_t *values_per_thread);
 /* Use configuration cfg for the grid n1 x n2 in this context (TM_EUNSUPPORTED
  * if it is not compiled for the grid). */
 int tm_set_config(tm_ctx *ctx, int32_t n1, int32_t n2, int32_t cfg);

@@ -35,7 +35,7 @@ EXPORTED = (
     "tm_pre_energy", "tm_pre_fiber_mask", "tm_pre_gather", "tm_amp_gradient", "tm_foci_power_ratio",
     "tm_dense_gradient", "tm_propagate_tm", "tm_phase_set_band", "tm_phase_last_counts",
     "tm_retrieve_noalloc", "tm_wnet_table", "tm_wnet_pretrain_step", "tm_wtab_power_grad", "tm_wnet_train_step",
-    "tm_set_weight_table", "tm_retrieve_learned", "tm_config_info", "tm_set_config", "tm_tune_config",
+    "tm_set_weight_table", "tm_retrieve_learned", "tm_config_info", "tm_config_kernel", "tm_set_config", "tm_tune_config",
     "tm_cgemm_f32", "tm_phase_offset_correct_async",
 )
 TM_NOALLOC_MAX_ROWS = 32768
@@ -151,6 +151,7 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.tm_tune_time.argtypes = [vp, i32, i32, i32, i32, i32, i32, i32, ctypes.POINTER(dp)]
     lib.tm_set_variant.argtypes = [vp, i32, i32, i32]
     lib.tm_config_info.argtypes = [i32, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32), ctypes.POINTER(i32)]
+    lib.tm_config_kernel.argtypes = lib.tm_config_info.argtypes
     lib.tm_set_config.argtypes = [vp, i32, i32, i32]
     lib.tm_cgemm_f32.argtypes = [vp, i32, i32, i32, vp, ctypes.c_int64, vp, ctypes.c_int64, i32, vp, ctypes.c_int64,
                                  i32, vp]
@@ -782,6 +783,27 @@ def tm_config_info(n1, n2, cfg):
     return (wg.value, rpw.value, ept.value) if ok else None
 
 
+def tm_config_kernel(n1, n2, cfg):
+    """(lowest configuration with the same kernels, their threads per workgroup,
+    rows per workgroup, values per thread) of launch configuration cfg (0..7),
+    or None if it is not compiled for the grid."""
+    if not isinstance(cfg, int) or isinstance(cfg, bool):
+        raise TMError("cfg must be an int")
+    wg, rpw, ept = ctypes.c_int32(0), ctypes.c_int32(0), ctypes.c_int32(0)
+    k = load().tm_config_kernel(int(n1), int(n2), int(cfg), ctypes.byref(wg), ctypes.byref(rpw), ctypes.byref(ept))
+    return (k, wg.value, rpw.value, ept.value) if k >= 0 else None
+
+
+def _kernels_revision() -> str:
+    """Digest of the library file: times taken on other kernels say nothing about these."""
+    import hashlib
+    h = hashlib.blake2b(digest_size=8)
+    with open(LIB_PATH, "rb") as fh:
+        for part in iter(lambda: fh.read(1 << 20), b""):
+            h.update(part)
+    return h.hexdigest()
+
+
 def tm_set_config(ctx: Context, n1, n2, cfg):
     ctx.check(ctx.lib.tm_set_config(ctx.h, n1, n2, cfg), "tm_set_config")
 
@@ -799,14 +821,15 @@ def autotune(ctx: Context, n1: int, n2: int, K: int, P: int, bf16: bool = False,
     """Choose the launch configuration of an n1 x n2 grid, apply it to the
     context and record it in the JSON cache `cache` (keyed by architecture,
     grid, K, intensity type and search space); a cached entry is applied
-    without timing.
+    without timing if it was taken on this library's kernels, else timed anew.
 
     space="digits": the two FFT digit orders, timed on the error-reduction
-    kernel over P rows (what the uneven batch takes).
+    kernel over P rows.
     space="full": every configuration compiled for the grid (digit order,
     eight or sixteen values per thread, one or two times the rows per
     workgroup, hence the waves per SIMD), each timed on the Lanczos step and
-    the cyclic ER step over P rows; the one with the least sum is applied."""
+    the cyclic ER step over P rows; the one with the least sum is applied.
+    Configurations with the same kernels (tm_config_kernel) are timed once."""
     import json
     if space not in ("digits", "full"):
         raise TMError(f"space {space!r} (digits or full)")
@@ -815,10 +838,14 @@ def autotune(ctx: Context, n1: int, n2: int, K: int, P: int, bf16: bool = False,
     if cache and os.path.exists(cache):
         with open(cache) as fh:
             table = json.load(fh)
-    if key in table:
+    revision = _kernels_revision()
+    cached = table.get(key, {}).get("kernels") == revision
+    if cached:
         entry = table[key]
     elif space == "digits":
-        times = [tm_tune_time(ctx, n1, n2, K, P, v, bf16, reps) for v in (0, 1)]
+        two = (tm_config_kernel(n1, n2, 1) or (1,))[0] == 1
+        times = [tm_tune_time(ctx, n1, n2, K, P, v, bf16, reps) for v in ((0, 1) if two else (0,))]
+        times += times[:1] * (2 - len(times))
         entry = {"variant": int(times[1] < times[0]), "us": times, "rows": P}
     else:
         # two rounds over the candidates, each keeping its faster round, so that
@@ -826,20 +853,28 @@ def autotune(ctx: Context, n1: int, n2: int, K: int, P: int, bf16: bool = False,
         cand = {}
         for rnd in range(2):
             for cfg in range(8):
-                shape = tm_config_info(n1, n2, cfg)
-                if shape is None:
+                kernel = tm_config_kernel(n1, n2, cfg)
+                if kernel is None:
+                    continue
+                if kernel[0] != cfg:
+                    cand[str(cfg)] = dict(cand[str(kernel[0])])
                     continue
                 lz, er = tm_tune_config(ctx, n1, n2, K, P, cfg, bf16, reps)
                 old = cand.get(str(cfg))
                 if old is None or lz + er < old["lanczos_us"] + old["er_cyclic_us"]:
-                    cand[str(cfg)] = {"lanczos_us": round(lz, 2), "er_cyclic_us": round(er, 2), "wg": shape[0],
-                                      "rows_per_wg": shape[1], "values_per_thread": shape[2]}
+                    cand[str(cfg)] = {"lanczos_us": round(lz, 2), "er_cyclic_us": round(er, 2), "wg": kernel[1],
+                                      "rows_per_wg": kernel[2], "values_per_thread": kernel[3]}
         best = min(cand, key=lambda k: cand[k]["lanczos_us"] + cand[k]["er_cyclic_us"])
         entry = {"config": int(best), "variant": int(best) & 1, "candidates": cand, "rows": P}
-    if cache and key not in table:
-        table[key] = entry
-        with open(cache, "w") as fh:
-            json.dump(table, fh, indent=1, sort_keys=True)
+    if cache and not cached:
+        entry["kernels"] = revision
+        had, table[key] = key in table, entry
+        try:
+            with open(cache, "w") as fh:
+                json.dump(table, fh, indent=1, sort_keys=True)
+        except PermissionError:  # a file that may only be read serves as before, but for its old times
+            if not had:
+                raise
     if "config" in entry:
         tm_set_config(ctx, n1, n2, entry["config"])
     else:

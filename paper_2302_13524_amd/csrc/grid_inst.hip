@@ -266,6 +266,18 @@ void TM_CAT(row_cfgshape, GL1, GL2)(int cfg, int* wg, int* rpw, int* ept) {
   }
 }
 
+// The lowest configuration whose kernels cfg runs (-1: not compiled), and their shape.
+int TM_CAT(row_cfgkernel, GL1, GL2)(int cfg, int* wg, int* rpw, int* ept) {
+  TM_CAT(row_cfgshape, GL1, GL2)(cfg, wg, rpw, ept);
+  if (*wg == 0) return -1;
+  if (cfg < 2) {
+    *wg = Launch<Default<0>>::WG;  // the same in both digit orders
+    *rpw = Launch<Default<0>>::RPW;
+    *ept = Default<0>::E;
+  }
+  return (cfg & 1) && (!kHasVar || (cfg < 2 && kWide)) ? cfg - 1 : cfg;
+}
+
 void TM_CAT(row_shape, GL1, GL2)(int* wg, int* rpw) {
   *wg = Launch<Default<0>>::WG;
   *rpw = Launch<Default<0>>::RPW;

@@ -14,6 +14,7 @@ namespace tmk {
   int row_launchc7_##a##_##b(int mode, int ibf16, const RowArgs& x, void* s); \
   int row_cfgmask_##a##_##b();                                                \
   void row_cfgshape_##a##_##b(int cfg, int* wg, int* rpw, int* ept);          \
+  int row_cfgkernel_##a##_##b(int cfg, int* wg, int* rpw, int* ept);          \
   void row_shape_##a##_##b(int* wg, int* rpw);
 TM_GRID_LIST(TM_DECL)
 
@@ -49,6 +50,14 @@ void row_cfg_shape(int L1, int L2, int cfg, int* wg, int* rpw, int* ept) {
 #define TM_CSHAPE(a, b) \
   if (L1 == a && L2 == b) { row_cfgshape_##a##_##b(cfg, wg, rpw, ept); return; }
   TM_GRID_LIST(TM_CSHAPE)
+}
+
+int row_cfg_kernel(int L1, int L2, int cfg, int* wg, int* rpw, int* ept) {
+  *wg = *rpw = *ept = 0;
+#define TM_CKERNEL(a, b) \
+  if (L1 == a && L2 == b) return row_cfgkernel_##a##_##b(cfg, wg, rpw, ept);
+  TM_GRID_LIST(TM_CKERNEL)
+  return -1;
 }
 
 void row_launch_shape(int L1, int L2, int* wg, int* rpw) {

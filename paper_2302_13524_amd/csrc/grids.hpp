@@ -19,6 +19,8 @@ row_launcher find_row_launcher(int L1, int L2, int cfg = 0);
 int row_cfg_mask(int L1, int L2);
 // workgroup threads, rows per workgroup and values per thread of a configuration (zeros if absent)
 void row_cfg_shape(int L1, int L2, int cfg, int* wg, int* rpw, int* ept);
+// lowest configuration whose kernels cfg runs (-1 if absent), with the shape of those kernels
+int row_cfg_kernel(int L1, int L2, int cfg, int* wg, int* rpw, int* ept);
 // threads per workgroup and rows per workgroup of a grid
 void row_launch_shape(int L1, int L2, int* wg, int* rpw);
 }  // namespace tmk

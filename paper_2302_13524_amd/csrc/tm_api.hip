@@ -1476,6 +1476,17 @@ extern "C" int tm_config_info(int32_t n1, int32_t n2, int32_t cfg, int32_t* wg, 
   return 1;
 }
 
+extern "C" int tm_config_kernel(int32_t n1, int32_t n2, int32_t cfg, int32_t* wg, int32_t* rows_per_wg,
+                                int32_t* values_per_thread) {
+  if (!tm_config_info(n1, n2, cfg, nullptr, nullptr, nullptr)) return -1;
+  int w = 0, r = 0, e = 0;
+  const int k = tmk::row_cfg_kernel(ilog2(n1), ilog2(n2), cfg, &w, &r, &e);
+  if (wg) *wg = w;
+  if (rows_per_wg) *rows_per_wg = r;
+  if (values_per_thread) *values_per_thread = e;
+  return k;
+}
+
 extern "C" int tm_set_config(tm_ctx* c, int32_t n1, int32_t n2, int32_t cfg) {
   if (!c) return TM_EINVAL;
   if (!tm_grid_supported(n1, n2)) return fail(c, TM_EUNSUPPORTED, "grid %dx%d", n1, n2);
