@@ -46,11 +46,11 @@ template <class PLg, typename IT>
 static bool launch_few(int mode, const RowArgs& a, dim3 grid, dim3 block, hipStream_t s) {
   switch (mode) {
     case M_GRAD:
-      if (a.sums) row_kernel_few<PLg, M_GRAD, IT, true><<<grid, block, 0, s>>>(a);
+      if (a.sums || a.fout) row_kernel_few<PLg, M_GRAD, IT, true><<<grid, block, 0, s>>>(a);
       else row_kernel_few<PLg, M_GRAD, IT, false><<<grid, block, 0, s>>>(a);
       return true;
     case M_AGRAD:
-      if (a.sums) row_kernel_few<PLg, M_AGRAD, IT, true><<<grid, block, 0, s>>>(a);
+      if (a.sums || a.fout) row_kernel_few<PLg, M_AGRAD, IT, true><<<grid, block, 0, s>>>(a);
       else row_kernel_few<PLg, M_AGRAD, IT, false><<<grid, block, 0, s>>>(a);
       return true;
     case M_ADJ:
@@ -111,7 +111,7 @@ static int launch_t(int mode, const RowArgs& a, hipStream_t s) {
       else row_kernel<PLg, M_ERC, IT, false><<<grid, block, 0, s>>>(a);
       break;
     case M_GRAD:
-      if (a.sums) row_kernel<PLg, M_GRAD, IT, true><<<grid, block, 0, s>>>(a);
+      if (a.sums || a.fout) row_kernel<PLg, M_GRAD, IT, true><<<grid, block, 0, s>>>(a);
       else row_kernel<PLg, M_GRAD, IT, false><<<grid, block, 0, s>>>(a);
       break;
     case M_SPEC: row_kernel<PLg, M_SPEC, IT><<<grid, block, 0, s>>>(a); break;
@@ -121,7 +121,7 @@ static int launch_t(int mode, const RowArgs& a, hipStream_t s) {
     case M_WBACK: row_kernel<PLg, M_WBACK, IT><<<grid, block, 0, s>>>(a); break;
     case M_LS: row_kernel<PLg, M_LS, IT><<<grid, block, 0, s>>>(a); break;
     case M_AGRAD:
-      if (a.sums) row_kernel<PLg, M_AGRAD, IT, true><<<grid, block, 0, s>>>(a);
+      if (a.sums || a.fout) row_kernel<PLg, M_AGRAD, IT, true><<<grid, block, 0, s>>>(a);
       else row_kernel<PLg, M_AGRAD, IT, false><<<grid, block, 0, s>>>(a);
       break;
     case M_ALS: row_kernel<PLg, M_ALS, IT><<<grid, block, 0, s>>>(a); break;
@@ -203,11 +203,11 @@ static int launch_x(int mode, const RowArgs& a, hipStream_t s) {
       else row_kernel_w<PX, M_ERC, IT, false, WG><<<grid, block, 0, s>>>(a);
       break;
     case M_GRAD:
-      if (a.sums) row_kernel_w<PX, M_GRAD, IT, true, WG><<<grid, block, 0, s>>>(a);
+      if (a.sums || a.fout) row_kernel_w<PX, M_GRAD, IT, true, WG><<<grid, block, 0, s>>>(a);
       else row_kernel_w<PX, M_GRAD, IT, false, WG><<<grid, block, 0, s>>>(a);
       break;
     case M_AGRAD:
-      if (a.sums) row_kernel_w<PX, M_AGRAD, IT, true, WG><<<grid, block, 0, s>>>(a);
+      if (a.sums || a.fout) row_kernel_w<PX, M_AGRAD, IT, true, WG><<<grid, block, 0, s>>>(a);
       else row_kernel_w<PX, M_AGRAD, IT, false, WG><<<grid, block, 0, s>>>(a);
       break;
     case M_ALS: row_kernel_w<PX, M_ALS, IT, true, WG><<<grid, block, 0, s>>>(a); break;

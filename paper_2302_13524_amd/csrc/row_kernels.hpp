@@ -51,7 +51,7 @@ struct RowArgs {
   float* vscale;           // [P] M_SPEC: scale of din (read), of the new previous iterate tin (written)
   void* yout;              // [P][K][N] (M_FWD_*)
   float* sums;             // [P][NSUM]
-  float* fout;             // M_GRAD, M_AGRAD: f written here [P] instead of into sums, or null
+  float* fout;             // M_GRAD, M_AGRAD: f written here [P] instead of into sums, or null (neither: no f)
   double* sums64;          // [P][2] (M_RES64)
   const float* rowmean;    // [P] mean of I per row (M_SPEC)
   float tau;               // M_SPEC truncation
@@ -1108,7 +1108,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
     if constexpr ((MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_AGRAD) && SUMS) {
       float out[NSUM];
       row_reduce<PL::T, WG, (MODE == M_ER || MODE == M_ERC) ? 2 : 1>(acc, red, tid, out);
-      if (valid && ltid == 0 && a.sums) {
+      if (valid && ltid == 0 && (a.sums || a.fout)) {
         if constexpr (MODE == M_ER || MODE == M_ERC) {
           gw(a.sums)[prow * NSUM + 0] = out[0];
           gw(a.sums)[prow * NSUM + 1] = out[1];

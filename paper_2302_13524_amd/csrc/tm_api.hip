@@ -396,14 +396,11 @@ static int gradient_mode(tm_ctx* c, int mode, tm_dims d, const tm_c32* masks, co
   if (!masks || !I || !t || !grad) return fail(c, TM_EINVAL, "null pointer argument");
   if (I_dtype != TM_F32 && I_dtype != TM_BF16) return fail(c, TM_EINVAL, "I_dtype %d", I_dtype);
   HIPCHK(c, hipSetDevice(c->device));
-  float* sums = (float*)ws_get(c, WS_SUMS, (size_t)d.P * tmk::NSUM * sizeof(float));
-  if (!sums) return fail(c, TM_ENOMEM, "workspace");
   tmk::RowArgs a = base_args(c, d, masks);
   a.I = I;
   a.tin = (const tmk::cx<float>*)t;
   a.tout = (tmk::cx<float>*)grad;
-  a.sums = sums;
-  a.fout = f;  // by the kernel itself: a copy out of the sums cost the smallest calls a second launch
+  a.fout = f;  // by the kernel itself: no workspace and, for the smallest calls, one launch less
   return run_row(c, fn, mode, I_dtype == TM_BF16, a, stream);
 }
 
