@@ -30,17 +30,17 @@ constexpr bool kWide = wide_compiled(GL1, GL2);
 template <int VAR>
 using Default = std::conditional_t<kWide, WidePlan<kWide ? GL1 : 6, kWide ? GL2 : 6>, Plan<GL1, GL2, -1, VAR>>;
 
-// Up to 2048 waves (two per SIMD) the mixed-axis kernels need no more than two waves'
-// registers, and take the form that loads a mask ahead. Lanczos step / gradient / training
-// backward step, 4 masks, us: 128 x 64, 64 rows 38.9 / 37.9 / 30.5 -> 35.7 / 34.6 / 25.7;
-// 64 x 64, 400 rows 35.3 / 33.7 / 74.0 -> 32.1 / 32.3 / 46.1; 64 x 32, 900 rows 34.6 /
-// 33.7 / 54.3 -> 31.8 / 31.7 / 46.5; 32 x 32, 512 rows 23.2 / 23.6 / 36.4 -> 22.0 / 22.3 /
-// 30.3. Adjoint, 6 masks: 32 x 32, 64 rows 21.1 -> 16.9, 64 x 32, 900 rows 31.6 -> 30.1; with
+// Up to eight waves per CU (two per SIMD, 2048 on 256 CUs) the mixed-axis kernels need no
+// more than two waves' registers, and take the form that loads a mask ahead. Lanczos step /
+// gradient / training backward step, 4 masks, us: 128 x 64, 64 rows 38.9 / 37.9 / 30.5 -> 35.7
+// / 34.6 / 25.7; 64 x 64, 400 rows 35.3 / 33.7 / 74.0 -> 32.1 / 32.3 / 46.1; 64 x 32, 900 rows
+// 34.6 / 33.7 / 54.3 -> 31.8 / 31.7 / 46.5; 32 x 32, 512 rows 23.2 / 23.6 / 36.4 -> 22.0 / 22.3
+// / 30.3. Adjoint, 6 masks: 32 x 32, 64 rows 21.1 -> 16.9, 64 x 32, 900 rows 31.6 -> 30.1; with
 // larger workgroups only to half as many waves (64 x 64, 256 rows 27.0 -> 25.9, 500 rows 33.6
-// -> 34.2). The L-BFGS line sums of 900 rows of 64 x 32, whose prologue has twice the loads
-// in flight, 64 -> 55. Error reduction gains nothing steady (averaged, 64 x 32, 900 rows: 33.9 -> 35.7;
-// cyclic level) and keeps the one form.
-constexpr int FEW_WAVES = 2048;
+// -> 34.2). The L-BFGS line sums of 900 rows of 64 x 32, whose prologue has twice the loads in
+// flight, 64 -> 55. Error reduction gains nothing steady (averaged, 64 x 32, 900 rows: 33.9 ->
+// 35.7; cyclic level) and keeps the one form.
+static int64_t few_waves(const RowArgs& a) { return 8 * (int64_t)a.cus; }
 
 template <class PLg, typename IT>
 static bool launch_few(int mode, const RowArgs& a, dim3 grid, dim3 block, hipStream_t s) {
@@ -54,7 +54,7 @@ static bool launch_few(int mode, const RowArgs& a, dim3 grid, dim3 block, hipStr
       else row_kernel_few<PLg, M_AGRAD, IT, false><<<grid, block, 0, s>>>(a);
       return true;
     case M_ADJ:
-      if (Launch<PLg>::WG > 128 && (int64_t)grid.x * (Launch<PLg>::WG / 64) > FEW_WAVES / 2) return false;
+      if (Launch<PLg>::WG > 128 && (int64_t)grid.x * (Launch<PLg>::WG / 64) > few_waves(a) / 2) return false;
       row_kernel_few<PLg, M_ADJ, IT><<<grid, block, 0, s>>>(a);
       return true;
     case M_LS: row_kernel_few<PLg, M_LS, IT><<<grid, block, 0, s>>>(a); return true;
@@ -93,7 +93,7 @@ static int launch_t(int mode, const RowArgs& a, hipStream_t s) {
   if (split_mode(mode) && (a.split < 1 || a.split > a.K)) return (int)hipErrorInvalidValue;
   dim3 grid((a.P + LC::RPW - 1) / LC::RPW * (split_mode(mode) ? a.split : 1)), block(LC::WG);
   if constexpr (PLg::WIDE) {
-    if ((int64_t)grid.x * (LC::WG / 64) <= FEW_WAVES && launch_few<PLg, IT>(mode, a, grid, block, s))
+    if ((int64_t)grid.x * (LC::WG / 64) <= few_waves(a) && launch_few<PLg, IT>(mode, a, grid, block, s))
       return (int)hipGetLastError();
   } else if constexpr (PLg::T == 512) {
     if ((int)grid.x <= a.cus && launch_two<PLg, IT>(mode, a, grid, block, s)) return (int)hipGetLastError();
