@@ -59,6 +59,7 @@ static bool launch_few(int mode, const RowArgs& a, dim3 grid, dim3 block, hipStr
       return true;
     case M_LS: row_kernel_few<PLg, M_LS, IT><<<grid, block, 0, s>>>(a); return true;
     case M_ALS: row_kernel_few<PLg, M_ALS, IT><<<grid, block, 0, s>>>(a); return true;
+    case M_FILT: row_kernel_few<PLg, M_FILT, IT><<<grid, block, 0, s>>>(a); return true;
     case M_SPEC: row_kernel_few<PLg, M_SPEC, IT><<<grid, block, 0, s>>>(a); return true;
     case M_LANCZOS: row_kernel_few<PLg, M_LANCZOS, IT><<<grid, block, 0, s>>>(a); return true;
     case M_LANCZOS_T: row_kernel_few<PLg, M_LANCZOS_T, IT><<<grid, block, 0, s>>>(a); return true;

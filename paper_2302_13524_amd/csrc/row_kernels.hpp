@@ -628,7 +628,8 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
   constexpr bool SMALL = !PL::WIDE && PL::N >= 256 && PL::N <= 512 && (MODE == M_GRAD || MODE == M_AGRAD);
   constexpr bool PF = (!PL::WIDE && (MODE == M_SPEC || MODE == M_LANCZOS || MODE == M_LANCZOS_T || MODE == M_WAPPLY)) ||
                       SMALL ||
-                      (W && FEW && MODE != M_WBACK && MODE != M_LS && MODE != M_ALS && MODE != M_ADJ);
+                      (W && FEW && (MODE == M_GRAD || MODE == M_AGRAD || MODE == M_SPEC || MODE == M_LANCZOS ||
+                                    MODE == M_LANCZOS_T || MODE == M_WAPPLY));
   constexpr bool AF = W && FEW && MODE == M_ADJ;  // the next spectrum loaded a mask ahead, the mask under the transform
   // Mixed-axis plan: at its 128 registers the compiler waits for each load in
   // turn (Lanczos step 419 us at 2286 x 8192, 294 in groups), so the loads are issued in
