@@ -38,6 +38,7 @@ struct BatchArgs {
   const BatchProb* probs;
   const BatchItem* items;
   int n_items;
+  int few;  // at most one item per CU
   int with_sums;         // pass the problems' sums pointers (else null)
   float tau, momentum, lower;
   float er_beta;         // ER Nesterov factor; t and t_prev alternate between t and vprev

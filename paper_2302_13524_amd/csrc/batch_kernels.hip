@@ -68,7 +68,7 @@ __device__ __forceinline__ S load_uniform(const S* p) {
 // One out-of-line body per specialisation, so that each gets its own register
 // allocation instead of the union of all of them. It builds the row arguments
 // of item `it` from the problem table (wave-uniform, so scalar loads).
-template <class PL, int M, int MODE, typename IT, bool SUMS>
+template <class PL, int M, int MODE, typename IT, bool SUMS, bool FEW>
 __device__ __attribute__((noinline)) void item_body(const BatchProb* probs, const BatchItem* items, int it,
                                                      const cx<float>* tw32, float tau, float momentum, float lower,
                                                      float er_beta, int swap, int lz_j, int lz_fuse, int lz_k,
@@ -94,6 +94,7 @@ __device__ __attribute__((noinline)) void item_body(const BatchProb* probs, cons
   a.din = oth;
   a.vscale = pr.vscale;
   a.I = pr.I;
+  a.fout = nullptr;
   a.yin = nullptr;
   a.yout = nullptr;
   a.sums = SUMS ? pr.sums : nullptr;
@@ -138,18 +139,19 @@ __device__ __attribute__((noinline)) void item_body(const BatchProb* probs, cons
   a.out_bf16 = 0;
   a.tw32 = wave_uniform(tw32);
   a.tw64 = nullptr;
-  row_body<PL, M, IT, SUMS, BATCH_WG, true>(a, w.blk, lds, red);
+  row_body<PL, M, IT, SUMS, BATCH_WG, true, FEW>(a, w.blk, lds, red);
 }
 
-template <int MODE, typename IT, bool SUMS>
-__global__ void __launch_bounds__(BATCH_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) batch_kernel(BatchArgs b) {
+template <int MODE, typename IT, bool SUMS, bool FEW>
+__global__ void __launch_bounds__(BATCH_WG) __attribute__((amdgpu_waves_per_eu(FEW ? 2 : 4, FEW ? 2 : 4)))
+batch_kernel(BatchArgs b) {
   __shared__ cx<float> lds[kLds];
   __shared__ float red[Launch<WidePlan<7, 6>, BATCH_WG>::RED_FLOATS];
   constexpr int M = (MODE == BATCH_ER) ? M_ER : (MODE == BATCH_ERC) ? M_ERC : (MODE == BATCH_LZ) ? M_LANCZOS : M_SPEC;
   for (int it = blockIdx.x; it < b.n_items; it += gridDim.x) {
     const int code = b.probs[b.items[it].prob].code;
 #define TM_ITEM(...)                                                                                      \
-  item_body<__VA_ARGS__, M, MODE, IT, SUMS>(b.probs, b.items, it, b.tw32, b.tau, b.momentum, b.lower, b.er_beta, \
+  item_body<__VA_ARGS__, M, MODE, IT, SUMS, FEW>(b.probs, b.items, it, b.tw32, b.tau, b.momentum, b.lower, b.er_beta, \
                                             b.swap, b.lz_j, b.lz_fuse, b.lz_k, lds, red)
     switch (code) {
       case 0: TM_ITEM(WidePlan<5, 5>); break;
@@ -163,11 +165,15 @@ __global__ void __launch_bounds__(BATCH_WG) __attribute__((amdgpu_waves_per_eu(4
   }
 }
 
+template <int MODE, typename IT, bool FEW>
+int launch_f(int with_sums, const BatchArgs& a, int grid, hipStream_t s) {
+  if (with_sums) batch_kernel<MODE, IT, true, FEW><<<grid, BATCH_WG, 0, s>>>(a);
+  else batch_kernel<MODE, IT, false, FEW><<<grid, BATCH_WG, 0, s>>>(a);
+  return (int)hipGetLastError();
+}
 template <int MODE, typename IT>
 int launch_m(int with_sums, const BatchArgs& a, int grid, hipStream_t s) {
-  if (with_sums) batch_kernel<MODE, IT, true><<<grid, BATCH_WG, 0, s>>>(a);
-  else batch_kernel<MODE, IT, false><<<grid, BATCH_WG, 0, s>>>(a);
-  return (int)hipGetLastError();
+  return a.few ? launch_f<MODE, IT, true>(with_sums, a, grid, s) : launch_f<MODE, IT, false>(with_sums, a, grid, s);
 }
 
 }  // namespace

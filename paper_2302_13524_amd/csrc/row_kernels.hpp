@@ -1109,13 +1109,13 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
     if constexpr ((MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_AGRAD) && SUMS) {
       float out[NSUM];
       row_reduce<PL::T, WG, (MODE == M_ER || MODE == M_ERC) ? 2 : 1>(acc, red, tid, out);
-      if (valid && ltid == 0 && (a.sums || a.fout)) {
-        if constexpr (MODE == M_ER || MODE == M_ERC) {
+      if constexpr (MODE == M_ER || MODE == M_ERC) {
+        if (valid && ltid == 0 && a.sums) {
           gw(a.sums)[prow * NSUM + 0] = out[0];
           gw(a.sums)[prow * NSUM + 1] = out[1];
-        } else {
-          gw(a.fout ? a.fout + prow : a.sums + prow * NSUM)[0] = out[0];
         }
+      } else {
+        if (valid && ltid == 0 && (a.sums || a.fout)) gw(a.fout ? a.fout + prow : a.sums + prow * NSUM)[0] = out[0];
       }
     }
   }

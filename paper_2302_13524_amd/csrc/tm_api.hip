@@ -1361,6 +1361,7 @@ extern "C" int tm_batch_create(tm_ctx* c, int32_t n, const tm_problem* probs, co
   int cus = 0;
   hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
   b->grid = std::max(1, std::min((int)items.size(), 2 * (cus > 0 ? cus : 256)));
+  b->args.few = (int)items.size() <= cus;
   if (use_graph) {
     hipError_t he = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
     if (he == hipSuccess) he = hipStreamBeginCapture(b->cap, hipStreamCaptureModeRelaxed);
