@@ -192,40 +192,39 @@ struct WidePlan {
 
 // --------------------------------------------------------------- butterflies
 // a, b <- a + w b, a - w b with w = W_16^K = exp(-2 pi j K / 16), K = 1 .. 3 (INV: conj w),
-// times -j (INV: +j) when ROT. w b = c u with c = cos(pi / 8), or sqrt(1/2) for K = 2, and
-// u = b's components with the tangent tan(pi / 8), or 1, between them: two operations for u
+// times -j (INV: +j) when ROT. w b = s u with s = sin(pi / 8), or sqrt(1/2) for K = 2, and
+// u = b's components with the cotangent cot(pi / 8), or 1, between them: two operations for u
 // and one fused multiply-add per result and component, each of which rounds its own value
 // once (Linzer and Feig's form for fused multiply-add machines; the difference as
 // 2 a - (a + w b), of the same length, takes over the sum's rounding). Error of a transform
-// against 64 bits, rms, forward / inverse, 1e-7: 128 x 64 1.204 / 1.206, one axis per pass
-// 1.235 / 1.234, differences from the sums 1.268 / 1.267; 32 x 32 1.043 / 1.052, 1.064 / 1.060,
+// against 64 bits, rms, forward / inverse, 1e-7: 128 x 64 1.164 / 1.170, one axis per pass
+// 1.235 / 1.234, differences from the sums 1.268 / 1.267; 32 x 32 1.016 / 1.019, 1.064 / 1.060,
 // 1.103 / 1.105.
 //
-// In FP32 the nearest values of both c are too small (by 3.1e-8 and 1.7e-8): with them alone
-// every transform loses that much gain (-4.5e-8 at 128 x 64), which moves a residual more
-// than its random rounding does. Half of the butterflies therefore take the next value up (of
-// sqrt(1/2) in one component, as it lies further off), and the gain comes to -0.8e-8. Of the
-// ways to choose the half this has the least error over the four grids, by 0.1 to 0.8 %.
-template <int K, bool INV, bool ROT, typename T>
+// Rounded constants also change a transform's gain, which moves a residual more than its
+// random rounding does. sin and cot(pi / 8) come out too large together (w by 1.7e-8; cos and
+// tan too small by 2.9e-8), sqrt(1/2) too small by 1.7e-8: with the nearest values the gain is
+// -2.2e-8. A radix-16 digit's last stage takes the next sqrt(1/2) up in one component (UP):
+// -1.2e-8 (one axis per pass -4.0e-8). In every stage it would be -0.1e-8, but the errors of
+// that value, 6.7e-8, would add 2 to 3 % to the random part.
+template <int K, bool INV, bool ROT, bool UP, typename T>
 __device__ __forceinline__ void bfly(cx<T>& a, cx<T>& b) {
-  constexpr bool up = sizeof(T) == 4 && ROT == (K != 1);
-  constexpr T t = T(0.41421356237309504880), r = T(0.70710678118654752440), c1 = T(0.92387953251128673848);
-  constexpr T cx_ = K == 2 ? r : up ? T(0.92387956380844116211) : c1;
-  constexpr T cy = K == 2 ? (up ? T(0.70710682868957519531) : r) : cx_;
+  constexpr T r = T(0.70710678118654752440), r_up = sizeof(T) == 4 ? T(0.70710682868957519531) : r;
+  constexpr T cot = T(2.41421356237309504880), sx = K == 2 ? r : T(0.38268343236508977173), sy = UP && K == 2 ? r_up : sx;
   T ux, uy;
   if constexpr (K == 1) {
-    ux = fmadd(INV ? -t : t, b.y, b.x);
-    uy = fmadd(INV ? t : -t, b.x, b.y);
+    ux = fmadd(cot, b.x, INV ? -b.y : b.y);
+    uy = fmadd(cot, b.y, INV ? b.x : -b.x);
   } else if constexpr (K == 2) {
     ux = INV ? b.x - b.y : b.x + b.y;
     uy = INV ? b.y + b.x : b.y - b.x;
   } else {
-    ux = fmadd(t, b.x, INV ? -b.y : b.y);
-    uy = fmadd(t, b.y, INV ? b.x : -b.x);
+    ux = fmadd(INV ? -cot : cot, b.y, b.x);
+    uy = fmadd(INV ? cot : -cot, b.x, b.y);
   }
   const T vx = !ROT ? ux : INV ? -uy : uy, vy = !ROT ? uy : INV ? ux : -ux;
-  b = cx<T>{fmadd(-cx_, vx, a.x), fmadd(-cy, vy, a.y)};
-  a = cx<T>{fmadd(cx_, vx, a.x), fmadd(cy, vy, a.y)};
+  b = cx<T>{fmadd(-sx, vx, a.x), fmadd(-sy, vy, a.y)};
+  a = cx<T>{fmadd(sx, vx, a.x), fmadd(sy, vy, a.y)};
 }
 // the same for w = 1
 template <bool INV, bool ROT, typename T>
@@ -262,8 +261,8 @@ __device__ __forceinline__ void dit_stage(cx<T>* u) {
         if constexpr (m >= 4) bfly1<INV, true, T>(v[q], v[q + h]);
       } else {
         auto turn = [&](auto n) {
-          bfly<decltype(n)::value, INV, false, T>(v[k], v[k + h]);
-          bfly<decltype(n)::value, INV, true, T>(v[k + q], v[k + q + h]);
+          bfly<decltype(n)::value, INV, false, m == 16, T>(v[k], v[k + h]);
+          bfly<decltype(n)::value, INV, true, m == 16, T>(v[k + q], v[k + q + h]);
         };
         switch (k * (16 / m)) {  // a constant of the unrolled loop
           case 1: turn(std::integral_constant<int, 1>{}); break;
