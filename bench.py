@@ -134,8 +134,9 @@ def parse():
     return args
 
 
-KERNEL_SOURCES = ["fft_core.hpp", "row_kernels.hpp", "grid_inst.hip", "grids.hpp"]
-LBFGS_SOURCES = ["lbfgs_kernels.hip", "lbfgs.hpp", "row_kernels.hpp", "fft_core.hpp", "grids.hpp"]  # with what it includes
+KERNEL_SOURCES = ["fft_core.hpp", "wide_fft.hpp", "row_kernels.hpp", "grid_inst.hip", "grids.hpp"]
+# with what it includes
+LBFGS_SOURCES = ["lbfgs_kernels.hip", "lbfgs.hpp", "row_kernels.hpp", "fft_core.hpp", "wide_fft.hpp", "grids.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_2286x8192.json")
 PHASE_EVAL_MARGIN = 2  # evaluations queued beyond the synchronous solve's count (the extra ones return at once)
 PIPE_BUFFERS = 3  # row buffers of the pipelined steps: retrieval i reuses the buffer of phase solve i - 3
@@ -160,12 +161,19 @@ def plan_tag(L1, L2, cfg):
     return f"Plan<{L1}, {L2}, {3 if cfg & 2 else -1}, {cfg & 1}>"
 
 
+def kernel_plans(L1, L2, cfg):
+    """The plans whose counters stand for configuration cfg: its one-axis plan,
+    and for configurations 0 and 1 the grid's mixed-axis plan."""
+    return [plan_tag(L1, L2, cfg)] + ([f"WidePlan<{L1}, {L2}>"] if cfg < 2 else [])
+
+
 def measured_traffic(P, N, plan=None):
     """HBM bytes per launch of the spectral and ER kernels from the committed
     FETCH_SIZE / WRITE_SIZE counter summary, scaled by the counters' reading
     for a device copy of known size; None when absent or taken on other
     sources; a row kernel's entry only when its counters were taken on `plan`
-    (the launch configuration's Plan<...>), if given."""
+    (the launch configuration's Plan<...>, or one of several), if given."""
+    plans = [plan] if isinstance(plan, str) else plan
     if not os.path.exists(TRAFFIC_FILE):
         return None
     with open(TRAFFIC_FILE) as fh:
@@ -178,7 +186,7 @@ def measured_traffic(P, N, plan=None):
           "lbfgs": d.get("lbfgs_sources_sha256") == sources_digest(LBFGS_SOURCES)}
     return {k: int(round((v["fetch_kib"] * fs + v["write_kib"] * ws) * 1024)) for k, v in d["kernels"].items()
             if ok["lbfgs" if k.startswith("lbfgs") else "row"]
-            and (plan is None or k.startswith("lbfgs") or v.get("plan") == plan)}
+            and (plans is None or k.startswith("lbfgs") or v.get("plan") in plans)}
 
 
 def pmc_summary(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, out):
@@ -202,7 +210,7 @@ def pmc_summary(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, out):
         # without sums; where several plans ran, the one with the most dispatches
         plans = {}
         for k in tab:
-            m = re.match(r"void tmk::row_kernel(?:_w)?<tmk::(Plan<7, 6, -?\d+, \d+>), (\d+), float, ", k)
+            m = re.match(r"void tmk::row_kernel(?:_w)?<tmk::(Plan<7, 6, -?\d+, \d+>|WidePlan<7, 6>), (\d+), float, ", k)
             if m and int(m.group(2)) == mode:
                 plans.setdefault(m.group(1), []).append(tab[k])
         plan = max(plans, key=lambda q: sum(c for _, c in plans[q]))
@@ -438,7 +446,7 @@ def main():
         tune = {"config": args.config}
     elif args.autotune:
         tune = tm.autotune(ctx, n1, n2, K, P, space="full", reps=5)
-        log(f"autotune {n1}x{n2}: config {tune['config']} {tm.tm_config_info(n1, n2, tune['config'])}")
+        log(f"autotune {n1}x{n2}: config {tune['config']} {tm.tm_config_kernel(n1, n2, tune['config'])[1:]}")
 
     def fidelity(t):
         c = torch.sum(torch.conj(t) * Tn, dim=1)
@@ -684,7 +692,7 @@ def main():
     # `roofline`. Both are bound by FP32 vector arithmetic (the FFT work), so the primary figure is
     # against the vector peak; the HBM view carries the algorithmic bytes and the counter-measured traffic.
     flops_row = 2 * K * 5 * N * np.log2(N) + 30 * K * N  # 2K FFTs + pointwise per row-step
-    wg_, rpw_, ept_ = tm.tm_config_info(n1, n2, tune["config"])
+    _, wg_, rpw_, ept_ = tm.tm_config_kernel(n1, n2, tune["config"])
     cfg_note = (f" [launch configuration {tune['config']}: {wg_} threads, {rpw_} row(s) per workgroup, "
                 f"{ept_} values per thread]")
     kernels = {
@@ -717,7 +725,7 @@ def main():
     extra_flops = {"er": er_extra_flops, "spectral": sp_extra_flops}
     for kv in kernels.values():
         kv["name"] += cfg_note
-    traffic = measured_traffic(P, N, plan_tag(n1.bit_length() - 1, n2.bit_length() - 1, tune["config"]))
+    traffic = measured_traffic(P, N, kernel_plans(n1.bit_length() - 1, n2.bit_length() - 1, tune["config"]))
     roofs = {}
     for key, kv in kernels.items():
         avg = kv["ms"] / max(kv["n"], 1)
@@ -779,7 +787,7 @@ def main():
                              "checked equal to the serial path" if args.pipeline else None},
         "lbfgs": {"iters_to_0.99": n_lb, "retrieval_ms": round(lb_ms, 3) if lb_ms else None},
         "roofline_lbfgs": roofline_lbfgs,
-        "autotune": {"config": tune["config"], "shape_wg_rows_values": tm.tm_config_info(n1, n2, tune["config"]),
+        "autotune": {"config": tune["config"], "shape_wg_rows_values": tm.tm_config_kernel(n1, n2, tune["config"])[1:],
                      "candidates_us": {c: [v["lanczos_us"], v["er_cyclic_us"]]
                                        for c, v in tune.get("candidates", {}).items()}},
         "lbfgs_amplitude": {"iters_to_0.99": n_la, "retrieval_ms": round(la_ms, 3) if la_ms else None},
@@ -1067,7 +1075,8 @@ def preprocess_variant(ctx, args):
 
 def batch_variant(ctx, args, pool=None):
     """Twelve TMs of uneven (N, P) in one persistent launch per iteration under
-    a captured HIP graph, BF16 intensities, digit order autotuned per grid.
+    a captured HIP graph, BF16 intensities (the plan has one kernel per grid,
+    whatever the tuner finds for single problems).
     With the host workers (pool), the intensities come from the oracle's
     forward model and a seeded sample of rows of every TM is retrieved by the
     FP64 oracle from the same BF16-rounded values, so that each TM reports

@@ -230,10 +230,12 @@ int tm_batch_destroy(tm_batch *b);
 /* Average device time (microseconds) of one error-reduction launch over P
  * rows of an n1 x n2 grid with K masks, FFT digit-order variant `variant`
  * (0: larger radices first, 1: smaller first), on synthetic data in library
- * workspace. */
+ * workspace. The two variants are the same kernels where tm_config_kernel
+ * gives 0 for configuration 1. */
 int tm_tune_time(tm_ctx *ctx, int32_t n1, int32_t n2, int32_t K, int32_t P, int32_t I_dtype,
                  int32_t variant, int32_t reps, double *us);
-/* Use digit-order variant `variant` for the grid n1 x n2 in this context. */
+/* Use digit-order variant `variant` for the grid n1 x n2 in this context (no
+ * effect where both are the same kernels). */
 int tm_set_variant(tm_ctx *ctx, int32_t n1, int32_t n2, int32_t variant);
 
 /* Launch configurations of the fused row kernels (the 2-D FFTs of Sec. 2.2,
@@ -528,7 +530,7 @@ int tm_pre_energy(tm_ctx *ctx, const void *stack, int32_t stack_dtype, int64_t n
  * raster index), whose summed energy first reaches frac (0 < frac <= 1) of
  * the total; an all-zero energy gives the empty set. pix [npix] int32
  * (device) receives the set in increasing raster order, *P_out (host) its
- * size. npix <= 8192 (the sort runs in one workgroup's LDS); energies must be
+ * size. npix <= 8192 (the running sums of one workgroup); energies must be
  * non-negative. Synchronous with respect to the host. */
 int tm_pre_fiber_mask(tm_ctx *ctx, const double *energy, int32_t npix, double frac, int32_t *pix,
                       int32_t *P_out, void *stream);

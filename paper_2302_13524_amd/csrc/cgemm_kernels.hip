@@ -21,10 +21,12 @@ namespace tmk {
 
 namespace {
 
-// Complex k from which the split product is taken. It costs a second, nearly empty
-// launch (k_cgemm_redo): 2-3 us. FP32 against split, us: 1024 x 1024 x 16 10.2 / 12.5,
-// 1024 x 1024 x 64 23.2 / 18.6, 2048 x 2048 x 48 23.5 / 25.1, 4096 x 4096 x 64 91 / 86,
-// 2286 x 2286 x 8192 4456 / 2335.
+// Complex k from which the split product is taken: it wins there at every size, while its
+// second, nearly empty launch (k_cgemm_redo, 2-3 us) makes it lose with few k. FP32 against
+// split, us: 1024 x 1024 x 16 10.1 / 12.3, x 64 25.5 / 15.0; 128 x 128 x 16 9.9 / 12.2;
+// 300 x 300 x 48 19.2 / 11.8, 2048 x 2048 x 64 28.6 / 22.5, 4096 x 4096 x 64 95 / 74,
+// 2286 x 2286 x 8192 4361 / 2690.
+// (At 32 the split would win by less, 1024 x 1024 15.3 / 12.0.)
 constexpr int SPLIT_K = 64;
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -180,9 +182,10 @@ __global__ void __launch_bounds__(256, 2) k_cgemm_mfma(CgemmArgs g) {
 }
 
 // ---------------------------------------------------------------- split products
-// The same product on the BF16 matrix cores (16 times the FP32 rate). Every FP32
-// value is the exact sum of three BF16 values, each the nearest to what the ones
-// before it leave,
+// The same product on the BF16 matrix cores (16 times the FP32 rate), after Henry, Tang
+// and Heinecke ("Leveraging the bfloat16 artificial intelligence datatype for
+// higher-precision computations", 2019). Every FP32 value is the exact sum of three BF16
+// values, each the nearest to what the ones before it leave,
 //   x = x1 + x2 + x3,  |x2| <= 2^-8 |x|,  |x3| <= 2^-17 |x|,
 // and a b = a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1) + (a2 b3 + a3 b2): eight
 // products that the FP32 sums take in exactly; a3 b3, at most 2^-34 of a b, is left
@@ -207,15 +210,14 @@ __global__ void __launch_bounds__(256, 2) k_cgemm_mfma(CgemmArgs g) {
 // infinities, the tile stops as soon as it has staged such a value and is left to
 // k_cgemm_redo (a NaN gives NaN in its row or column either way). With a range per value
 // in place of the scaling, [2^-48, 2^48], one sine of pi in a row of phases sent its tiles
-// there: 2286 x 2286 x 8192 with phases of 0 and pi took 4390 us, so
-// 2404.
+// there: 2286 x 2286 x 8192 with phases of 0 and pi took 4390 us, now 2400 to 2520.
 //
 // 128 x 64 tiles and three workgroups per CU (168 VGPRs, 48 KB of LDS): 2286 x 2286
 // has 648 of them for 768 places, where 128 x 128 tiles at two per CU would leave a
 // third of the chip idle. The operands are split while they are staged, so nothing
 // is read twice and no workspace is kept; B is stored once for C_r and once for C_i.
-// 2588 us at 2286 x 2286 x 8192 (FP32 cores 4361): 1060 TFLOP/s of BF16 products, with
-// the splitting (VALU) beside them.
+// 2590 to 2690 us at 2286 x 2286 x 8192 (FP32 cores 4361): 1020 to 1060 TFLOP/s of BF16
+// products, with the splitting (VALU) beside them.
 constexpr int SN = 64;                                        // tile columns
 constexpr int S_PLANE_A = TM * TK, S_PLANE_B = SN * TK;  // words (two BF16) of a plane
 

@@ -281,10 +281,10 @@ struct Where<PL, true> {
 };
 
 // Access to value `lane + reg` of an array at p, `reg` a constant of the
-// register. With 32 values per thread p is the same in every lane and the
+// register. With the mixed-axis plan (W) p is the same in every lane and the
 // access is a buffer one: one 32-bit offset per lane, the register's part in
-// the instruction or a scalar. As global accesses the compiler kept 32 64-bit
-// addresses per array in registers across the mask loop (120 to 200 spilled).
+// the instruction or a scalar. As global accesses the compiler keeps a 64-bit
+// address per value and array in registers across the mask loop.
 typedef unsigned tm_v2u __attribute__((ext_vector_type(2)));
 template <typename V>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const V* p) {
@@ -356,7 +356,7 @@ template <class PL, typename T, bool TWO>
 struct FftOf<PL, T, TWO, true> { using type = WideFft<PL, T>; };
 
 // Shape of one workgroup of WGT threads (default: one row of T threads, at
-// least 256 threads; with 32 values per thread at least one wave).
+// least 256 threads; with the mixed-axis plan at least one wave).
 template <class PL>
 constexpr int default_wg() {
   constexpr int least = PL::WIDE ? 64 : 256;
@@ -424,7 +424,7 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
                                       a.tw32 + (PL::N1 - 1),
                                       a.tw32 + (PL::N2 - 1));
   const Where<PL> at(ltid);
-  // Arrays of the row: with 32 values per thread their bases are those of the
+  // Arrays of the row: with the mixed-axis plan their bases are those of the
   // workgroup's first row (the same in every lane; an invalid row reads that
   // one) and the row's distance goes into the lane offsets.
   constexpr bool W = PL::WIDE;
@@ -622,9 +622,10 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
   // 2286 x 8192). The ER and gradient steps load the mask twice and the
   // intensities after the transform: the same changes measured slower there
   // (cyclic ER 0.357 -> 0.376 and 0.413 ms).
-  // The gradients load ahead on the 16 x 16 grid's plan (200 rows 19.9 -> 17.6 us, 20000
-  // rows 72.0 -> 61.9); with 8 x 8 rows nothing is gained (24.2 -> 26.9 at 20000 rows), and
-  // the large one-axis plans' registers do not hold the values.
+  // The gradients load ahead on the plans of 256 and 512 points (16 x 16, 200 rows 19.9 ->
+  // 17.6 us, 20000 rows 72.0 -> 61.9; 8 x 32, 20000 rows 124 -> 87); with 8 x 8 rows nothing is
+  // gained (24.2 -> 26.9 at 20000 rows), and the large one-axis plans' registers do not hold
+  // the values.
   constexpr bool SMALL = !PL::WIDE && PL::N >= 256 && PL::N <= 512 && (MODE == M_GRAD || MODE == M_AGRAD);
   constexpr bool PF = (!PL::WIDE && (MODE == M_SPEC || MODE == M_LANCZOS || MODE == M_LANCZOS_T || MODE == M_WAPPLY)) ||
                       SMALL ||
@@ -639,7 +640,8 @@ __device__ __forceinline__ void row_body(const RowArgs& args, int wgi, cx<float>
   // pass and half after it.
   // One-axis plan of 8192 points (64 x 128): left to itself the compiler saves registers for
   // a second workgroup per CU that does not fit and waits for each load (error reduction of
-  // 1000 rows 245 us, in groups 173). Where it groups them itself it is left alone.
+  // 1000 rows 245 us, in groups 173; 170 with two LDS copies, where it did not). In the other
+  // forms it groups them itself.
   constexpr bool GRP = !W && !OOL && PL::T == 512 && PL::E == 16 &&
                        (MODE == M_ER || (MODE == M_GRAD && !SUMS) || (MODE == M_AGRAD && (!SUMS || sizeof(IT) == 2)));
   constexpr bool WI = GRP || (W && !PF && (MODE == M_ER || MODE == M_ERC || MODE == M_GRAD || MODE == M_SPEC ||
