@@ -111,3 +111,27 @@ def test_single_products_of_any_scale(ctx, ea, eb):
     C = _product(ctx, A, B).real.astype(np.float64)
     ref = A.real.astype(np.float64) @ B.real.astype(np.float64).T
     assert np.all(np.abs(C - ref) <= 2.0**-24 * (1 + 2.0**-8) * np.abs(ref) + 2.0**-149)
+
+
+@pytest.mark.parametrize("trans_b", [False, True])
+@pytest.mark.parametrize("M,N,K,pad", [(130, 70, 81, 1), (129, 65, 64, 3), (5, 200, 97, 10)])
+def test_padded_rows(ctx, M, N, K, pad, trans_b):
+    # leading dimensions beyond the operands' rows (NaN between them), and a result with room
+    # between its rows, which stays
+    g = np.random.default_rng(pad)
+    A = (g.standard_normal((M, K)) + 1j * g.standard_normal((M, K))).astype(np.complex64)
+    B = (g.standard_normal((N, K)) + 1j * g.standard_normal((N, K))).astype(np.complex64)
+    Bd = B if trans_b else B.T
+
+    def padded(x):
+        out = torch.full((x.shape[0], x.shape[1] + pad), float("nan"), dtype=torch.complex64)
+        out[:, :x.shape[1]] = torch.from_numpy(np.ascontiguousarray(x))
+        return out.to(dev())
+
+    Ap, Bp = padded(A), padded(Bd)
+    C = torch.full((M, N + pad), 7.0, dtype=torch.complex64, device=dev())
+    rc = ctx.lib.tm_cgemm_f32(ctx.h, M, N, K, Ap.data_ptr(), K + pad, Bp.data_ptr(), Bp.shape[1], int(trans_b),
+                              C.data_ptr(), N + pad, 0, torch.cuda.current_stream(dev()).cuda_stream)
+    assert rc == tm.TM_OK
+    C = C.cpu().numpy()
+    assert np.array_equal(C[:, :N], _product(ctx, A, B, trans_b)) and np.all(C[:, N:] == 7.0)
